@@ -109,7 +109,8 @@ typedef struct lt_options {
                               whose splits share one threshold (for those shapes
                               rounded up to a multiple of 16: their lists are
                               stored in chunks of 16 entries)                  */
-  int32_t key_splits;      /* key-range splits per row; 0 = auto (fused), 1 (scores-in) */
+  int32_t key_splits;      /* key-range splits per row; 0 = auto (scores-in: 1 from 256
+                              rows on)                                           */
   uint32_t flags;          /* LT_SORTED_OUTPUT | LT_FORCE_FALLBACK               */
   uint64_t seed;           /* seed of the key sample                             */
   void** stage_events;     /* NULL, or LT_NUM_STAGE_EVENTS hipEvent_t handles     */

@@ -29,6 +29,8 @@ constexpr int kMaxAutoSplits = 64;
 constexpr size_t kHistLdsBudget = 96 * 1024;
 constexpr size_t kLdsPerBlock = 160 * 1024;   // gfx950 LDS per workgroup
 constexpr int kSampleBlockScores = 64;      // scores-in sample: runs of 64 consecutive keys
+constexpr int kMinScoresSplitKeys = 16384;  // shortest key split the scores-in entry makes by itself:
+constexpr int kMinScoresSplitK = 32;        // these keys, and this many times k
 constexpr int kMinSharedSplitKeys = 1024;   // shortest key split of the shared-row (wide) scan
 constexpr int kSharedSample = 65536;        // default sample of the shared-row scan (inner product)
 
@@ -205,12 +207,20 @@ Resolved resolve_scores(const lt_options* o, int nq, int nk, int k) {
   if (!o) o = &d;
   r.ns = resolve_sample(o, r, nk, k, LT_SCORE_DSA, false);
   int S = 1;
-  if (o->key_splits > 0) S = o->key_splits;
+  if (o->key_splits > 0) {
+    S = o->key_splits;
+  } else if (nq > 0 && nq < kTargetBlocks) {
+    // few rows: splits up to a block per CU. Each refreshes its own
+    // threshold and keeps about k (1 + ln(keys / 3k)) candidates, so short
+    // splits cost the select more than they save here: at least
+    // kMinScoresSplitKeys keys and kMinScoresSplitK * k
+    S = std::min({(kTargetBlocks + nq - 1) / nq, nk / kMinScoresSplitKeys, nk / kMinScoresSplitK / k});
+  }
   r.S = std::max(1, std::min(S, (nk + 255) / 256 + 1));
   r.HS = r.S;
   const int per = (nk + r.S - 1) / r.S;
   r.L = std::max(256, ((per + 255) / 256) * 256);
-  (void)nq;
+  r.cap = std::min(r.cap, r.L);  // a split never holds more candidates than keys
   return r;
 }
 

@@ -1,5 +1,7 @@
 // Selection-side kernels: per-row range from the sample, the scores-in
 // filter scan, the final select, the exact fallback and plain radix select.
+#include <type_traits>
+
 #include "internal.hpp"
 #include "select_dev.hpp"
 
@@ -174,91 +176,140 @@ __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride,
 
 // ---------------------------------------------------------------------------
 // Scores-in filter scan (sec. 3.2 "Filtering" + "Threshold Refresh"). One
-// wave owns one (row, key split): it streams its scores once, gates them with
-// the row's current threshold bin, appends the passing ones (ballot + mbcnt
-// compaction, one write per passing key, key order preserved) to its own
-// candidate list and counts them in its own LDS histogram. The threshold is
-// kept current after every chunk of 256 keys with the running count of
-// candidates above it (see FusedSink in score.hip). A list that reaches `cap`
-// stops storing but keeps counting, so the final select can detect the
-// overflow.
+// block owns one (row, key split): it streams its scores once in steps of
+// NTH * U keys, wave w of a step taking the w-th run of kWave * U
+// consecutive keys, gates them with the row's current
+// threshold bin, appends the passing ones to the split's candidate list in
+// key order (a ballot per 64 keys; the waves exchange their step totals
+// through LDS, one barrier a step) and counts them in the block's LDS
+// histogram. A list that reaches `cap` stops storing but keeps counting, so
+// the final select can detect the overflow.
+// Threshold refresh: a step counts its passing keys in the histogram first.
+// Once kRefreshShare-th of k new ones have been counted, every wave walks the
+// histogram to the new threshold and the step's keys are gated again before
+// they are written, so that a step as long as a short row keeps no more than
+// a fine-grained scan would.
+// The splits of a row cut its visible range into even parts and keep their
+// own thresholds: reading each other's from global memory stalled every
+// refresh (128 rows x 131072 in two splits: 158 us a call against 76) and
+// came too late in short splits, so the host makes few and long ones
+// (resolve_scores).
+// Bound by HBM: the loads of the next step (4 U bytes a thread) are in flight
+// while the current one is gated, and the block is as wide as it takes to keep
+// four waves per SIMD resident (launch_filter).
+// 1024 rows of 262144 scores (1.07 GB), k = 2048: 1078 us with one wave per
+// row and one load in flight, 282 us so (3.8 TB/s).
 // ---------------------------------------------------------------------------
-constexpr int kFilterWaves = 4;
+constexpr int kRefreshShare = 4;
+constexpr int kFilterLong = 32768;  // splits of this many keys take 16 keys per thread and step, shorter ones 8
 
-__global__ __launch_bounds__(kFilterWaves * kWave) void k_filter(
-    const float* scores, int64_t stride, int nq, int nk, const int32_t* offs, const int32_t* starts,
-    const RowParam* params, int S, int L, int cap, int m, int k, uint32_t* cnt, uint32_t* hist_out, int2* cand) {
-  __shared__ uint32_t hist_all[kFilterWaves][kMaxBins];
-  const int wave = threadIdx.x / kWave, l = lane_id();
-  const int unit = blockIdx.x * kFilterWaves + wave;
-  if (unit >= nq * S) return;
-  const int row = unit / S, split = unit - row * S;
-  uint32_t* hist = hist_all[wave];
+template <int NTH, int U>
+__global__ __launch_bounds__(NTH) void k_filter(const float* scores, int64_t stride, int nq, int nk,
+                                                const int32_t* offs, const int32_t* starts, const RowParam* params,
+                                                int S, int L, int cap, int m, int k, uint32_t* cnt,
+                                                uint32_t* hist_out, int2* cand) {
+  constexpr int NW = NTH / kWave, STEP = NTH * U;
+  __shared__ uint32_t hist[kMaxBins];
+  __shared__ uint32_t wtot[3][NW];  // the waves' passing keys: steps in turn, a step gated again
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), l = lane_id();
+  const int unit = blockIdx.x, row = unit / S, split = unit - row * S;
   const RowRange rr = row_range(offs, starts, row, nk);
-  // the split's keys within the row's range; the first chunk starts on a
-  // 4-key boundary for the float4 loads, keys below the range are masked
-  const int lo = max(split * L, rr.s & ~3);
-  const int hi = min(split * L + L, rr.e);
-  const int klo = max(split * L, rr.s);
+  // the split's share of the row's range (at most L keys)
+  const int part = min(L, ((rr.e - rr.s + S - 1) / S + 255) & ~255);
+  const int lo = rr.s + min(split * part, rr.e - rr.s), hi = min(lo + part, rr.e);
   const RowParam p = params[row];
-  int tau = p.tau0;
-  float thr = gate_thr(tau);
-  float thr_up = tau < m - 1 ? (float)(tau + 1) : __builtin_nanf("");
-  uint32_t above = 0;
-  for (int b = l; b < kMaxBins; b += kWave) hist[b] = 0u;
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  float thr = gate_thr(p.tau0);
+  for (int b = threadIdx.x; b < kMaxBins; b += NTH) hist[b] = 0u;
+  __syncthreads();
 
-  const float* rp = scores + (int64_t)row * stride;
   int2* out = cand + (int64_t)unit * cap;
-  uint32_t tail = 0;
-  for (int base = lo; base < hi; base += 4 * kWave) {
-    const int i0 = base + 4 * l;
-    float v[4];
-    if (i0 + 3 < hi) {
-      float4 t = *reinterpret_cast<const float4*>(rp + i0);
-      v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-    } else {
+  uint32_t tail = 0, fresh = 0;
+  const uint32_t refresh_at = max((uint32_t)k / kRefreshShare, 8u);
+  const int len = hi - lo;
+  // a descriptor per step whose range check turns the keys past hi into
+  // zeros without a branch (they are masked below)
+  const uint64_t base = (uint64_t)(scores + (int64_t)row * stride + lo);
+  const float* ubase = (const float*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)base) |
+                                      (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32);
+  const int ulen = __builtin_amdgcn_readfirstlane(len);
+  const int woff = wave * kWave * U;  // the wave's keys of a step: [step + woff, + kWave * U)
+  auto load = [&](int off, float (&v)[U]) {
+    const int left = ulen - off - woff;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(ubase + off + woff), 0, left > 0 ? (int)((uint32_t)min(left, kWave * U) * 4u) : 0, kBufferRaw);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = (i0 + j < hi) ? rp[i0 + j] : 0.0f;
+    for (int u = 0; u < U; ++u)
+      v[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, l * 4 + u * kWave * 4, 0, 0));
+  };
+  int par = 0;
+  // the waves' totals: this wave's offset in the step and the step's total
+  uint32_t before = 0, total = 0;
+  auto exchange = [&](uint32_t* tot, uint32_t mine) {
+    if (l == 0) tot[wave] = mine;
+    __syncthreads();
+    before = total = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)tot[w]);
+      before += w < wave ? t : 0u;
+      total += t;
     }
-    float x[4];
-    bool ps[4];
-    uint32_t below = 0, total = 0, up = 0;
+  };
+  auto step = [&](int off, const float (&v)[U]) {
+    const int rel = off + woff + l;  // position of item 0 in the split
+    uint32_t bits = 0, mine = 0;     // bit u: item u passes; the wave's passing keys
+    auto gate = [&]() {
+      bits = mine = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      x[j] = bin_x(v[j], p.delta, p.c);
-      ps[j] = (i0 + j >= klo) && (i0 + j < hi) && !(x[j] < thr);
-      uint64_t mask = __ballot(ps[j]);
-      below += mbcnt64(mask);
-      total += (uint32_t)__popcll(mask);
-      up += (uint32_t)__popcll(__ballot(ps[j] && x[j] >= thr_up));
+      for (int u = 0; u < U; ++u) {
+        const bool ps = (rel + u * kWave < ulen) & !(bin_x(v[u], p.delta, p.c) < thr);
+        mine += (uint32_t)__popcll(__ballot(ps));
+        bits |= (uint32_t)ps << u;
+      }
+    };
+    gate();
+    if (mine != 0) {  // wave-uniform
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int b = bin_of(bin_x(v[u], p.delta, p.c), m);
+        if (((bits >> u) & 1u) && b >= 0) atomicAdd(&hist[b], 1u);
+      }
     }
-    if (total == 0) continue;  // wave-uniform
-    uint32_t pos = tail + below;
+    exchange(wtot[par], mine);
+    par ^= 1;
+    fresh += total;
+    if (fresh >= refresh_at) {  // block-uniform; no wave counts again before the exchange below
+      fresh = 0;
+      thr = fmaxf(thr, gate_thr(wave_threshold(hist, m, (uint32_t)k, nullptr)));
+      gate();
+      exchange(wtot[2], mine);
+    }
+    if (mine != 0) {
+      uint32_t at = tail + before;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (ps[j]) {
-        if (pos < (uint32_t)cap) out[pos] = make_int2(i0 + j, __float_as_int(v[j]));
-        int b = bin_of(x[j], m);
-        if (b >= 0) atomicAdd(&hist[b], 1u);
-        ++pos;
+      for (int u = 0; u < U; ++u) {
+        const bool ps = (bits >> u) & 1u;
+        const uint64_t mask = __ballot(ps);
+        const uint32_t pos = at + mbcnt64(mask);
+        if (ps && pos < (uint32_t)cap) out[pos] = make_int2(lo + rel + u * kWave, __float_as_int(v[u]));
+        at += (uint32_t)__popcll(mask);
       }
     }
     tail += total;
-    above += up;
-    if (above >= (uint32_t)k) {
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      while (above >= (uint32_t)k && tau < m - 1) {
-        ++tau;
-        above -= hist[tau];
-      }
-      thr = gate_thr(tau);
-      thr_up = tau < m - 1 ? (float)(tau + 1) : __builtin_nanf("");
+  };
+  if (ulen > 0) {
+    float va[U], vb[U];
+    load(0, va);
+    for (int off = 0; off < ulen; off += 2 * STEP) {
+      load(off + STEP, vb);
+      step(off, va);
+      load(off + 2 * STEP, va);
+      step(off + STEP, vb);
     }
   }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  for (int b = l; b < m; b += kWave) hist_out[(int64_t)unit * m + b] = hist[b];
-  if (l == 0) cnt[unit] = tail;
+  __syncthreads();
+  for (int b = threadIdx.x; b < m; b += NTH) hist_out[(int64_t)unit * m + b] = hist[b];
+  if (threadIdx.x == 0) cnt[unit] = tail;
 }
 
 // ---------------------------------------------------------------------------
@@ -775,10 +826,21 @@ hipError_t launch_range(bool from_scores, const float* src, int64_t stride, int 
 hipError_t launch_filter(const float* scores, int64_t stride, int nq, int nk, const int32_t* offs,
                          const int32_t* starts, const RowParam* params, int S, int L, int cap, int m, int k,
                          uint32_t* cnt, uint32_t* hist, int2* cand, hipStream_t st) {
+  auto go = [&](auto kernel, int nth) {
+    hipLaunchKernelGGL(kernel, dim3(nq * S), dim3(nth), 0, st, scores, stride, nq, nk, offs, starts, params, S, L,
+                       cap, m, k, cnt, hist, cand);
+  };
+  // 16 waves per CU: one block of 1024 threads, two of 512 or four of 256
   const int units = nq * S;
-  dim3 grid((units + kFilterWaves - 1) / kFilterWaves);
-  hipLaunchKernelGGL(k_filter, grid, dim3(kFilterWaves * kWave), 0, st, scores, stride, nq, nk, offs, starts,
-                     params, S, L, cap, m, k, cnt, hist, cand);
+  if (units == 0) return hipSuccess;
+  auto by_len = [&](auto U) {
+    constexpr int u = decltype(U)::value;
+    if (units >= 1024) go(k_filter<256, u>, 256);
+    else if (units >= 512) go(k_filter<512, u>, 512);
+    else go(k_filter<1024, u>, 1024);
+  };
+  if (L >= kFilterLong) by_len(std::integral_constant<int, 16>{});
+  else by_len(std::integral_constant<int, 8>{});
   return hipGetLastError();
 }
 

@@ -1,0 +1,67 @@
+"""The selection kernels at the edges of their dispatch: the scores-in filter's
+block widths and step lengths, rows gathered and ordered by distribution (and
+the rows that leave that way for the general sort), radix selection over a
+row's own span, and the union's bitmap and its span limit. Everything is
+compared bit for bit with the oracle: the selections compute no score."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import litetopk_oracle as orc
+from paper_2607_11976_amd import litetopk as lt
+from paper_2607_11976_amd import workloads
+from parity import check_row_exact
+from helpers import oracle_topk, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(kind, nq, nk, seed):
+    rng = np.random.default_rng(seed)
+    if kind in ("normal", "ties", "special", "const"):
+        return workloads.score_rows(nq, nk, seed=seed, kind=kind, ld=(nk + 3) // 4 * 4)
+    s = np.empty((nq, (nk + 3) // 4 * 4), dtype=np.float32)
+    if kind == "ascending":        # every key passes the gate: overflow
+        s[:, :nk] = np.arange(nk, dtype=np.float32)
+    elif kind == "narrow":         # one binade, neighbours a few ulps apart
+        s[:, :nk] = (1.5 + rng.integers(0, 1 << 16, size=(nq, nk)) * 2.0 ** -22).astype(np.float32)
+    elif kind == "heavy":          # a distribution that no linear map spreads
+        s[:, :nk] = np.exp(np.clip(20 * rng.standard_normal((nq, nk)), -87, 88)).astype(np.float32)
+    elif kind == "infs":           # more infinities than k, both signs
+        s[:, :nk] = rng.choice([np.inf, -np.inf, 0.0, -0.0, np.nan, 1.0], size=(nq, nk))
+    return torch.from_numpy(s)
+
+
+def _check(scores, nk, k, offs, starts, gi, gs, sorted_out, rows):
+    s = scores.numpy()[rows]
+    o = None if offs is None else offs[rows]
+    st = None if starts is None else starts[rows]
+    ri, rs = orc.topk_select(s, nk, k, o, visible_start=st)
+    s0, e0 = orc.visible_ranges(o, st, len(rows), nk)
+    for j, t in enumerate(rows):
+        check_row_exact(gi[t], gs[t], ri[j], rs[j], int(e0[j] - s0[j]), k, sorted_out)
+
+
+# block widths follow the rows (1024, 512 and 256 threads from 1, 512 and 1024
+# units), steps the split's length (32768 keys); fewer than 256 rows split
+@pytest.mark.parametrize("nq,nk,k,kind", [
+    (1, 140001, 100, "normal"),
+    (3, 70000, 2048, "ascending"),
+    (20, 33000, 7, "narrow"),
+    (300, 32767, 64, "ties"),
+    (513, 8193, 300, "special"),
+    (1025, 4099, 100, "infs"),
+    (1024, 40003, 16, "heavy"),
+    (130, 257, 300, "normal"),
+])
+@pytest.mark.parametrize("sorted_out", [False, True])
+def test_scores_in_filter_shapes(lib, nq, nk, k, kind, sorted_out):
+    scores = _rows(kind, nq, nk, seed=nq + k)
+    rng = np.random.default_rng(nk)
+    offs = workloads.causal_offsets(nq, nk)
+    starts = rng.integers(0, max(1, nk // 3), size=nq).astype(np.int32)  # not multiples of anything
+    o, st = torch.from_numpy(offs).cuda(), torch.from_numpy(starts).cuda()
+    gi, gs = lt.topk_select(scores.cuda(), k, nk, o, options=lt.make_options(sorted_output=sorted_out,
+                                                                             visible_start=st))
+    gi, gs = gi.cpu().numpy(), gs.cpu().numpy()
+    _check(scores, nk, k, offs, starts, gi, gs, sorted_out, sorted({0, 1 % nq, nq // 2, nq - 1}))
