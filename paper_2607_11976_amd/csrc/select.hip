@@ -345,6 +345,134 @@ constexpr int kRankMax = 512;
 // LDS byte offset of the sort entries of k_select with NTH threads.
 constexpr size_t select_ent_offset(int nth) { return ((size_t)kMaxBins + 32 + nth + 16) * 4; }
 
+// Sorted rows. Their final order does not depend on the order in which the
+// candidates arrive, so the keys at or above bin tau (k plus part of one bin)
+// are gathered into LDS by independent waves and ordered there by
+// order_entries, where a gather in list order, block-wide step by step, and a
+// bitonic sort took twice as long (4096 rows of 8.7 K candidates, k = 2048:
+// 314 -> 149 us; 10000 rows of 1.1 K, k = 100: 231 -> 125 us).
+// Rows that order_entries does not take, or with more than sort_slots(E) keys,
+// take the general path, whose sort does not depend on the values.
+//
+// nmax: keys at or above bin tau by the histograms. Returns 0 when the row is
+// written, 1 when the lists disagree with the histograms (the fallback's), -1
+// for the general path. tmp[26] ends as the keys gathered, tmp[27] as those
+// above bin tau.
+template <int NTH, int PER>
+__device__ __forceinline__ int select_sorted(int row, const RowParam& p, const uint32_t* cnt, const int2* cand, int nq,
+                                             int S, int cap, int m, int k, int E, bool keyed, bool ilv, int tau,
+                                             uint32_t c_above, uint32_t nmax, uint32_t* tmp, uint32_t* off,
+                                             uint64_t* ent, int32_t* oi, float* os) {
+  constexpr int NW = NTH / kWave, EPT = 12;  // entries per thread: sort_slots(E) / NTH at most (launch_select)
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), l = lane_id();
+  const uint32_t slots = (uint32_t)sort_slots(E);
+  const int NB = bucket_count<NTH>(nmax, E);
+  int2* e2 = reinterpret_cast<int2*>(ent);
+  uint32_t* bk = reinterpret_cast<uint32_t*>(ent + slots);  // [NB]
+  float* red = reinterpret_cast<float*>(off);               // [2 * NW]
+  for (int b = tid; b < NB; b += NTH) bk[b] = 0u;
+  if (tid == 0) {
+    tmp[26] = 0u;
+    tmp[27] = 0u;
+  }
+  __syncthreads();
+
+  // ---- gather ----
+  float mn = __builtin_inff(), mx = -__builtin_inff();
+  uint32_t wab = 0;  // the wave's keys above bin tau
+  // positions p0 + u * ll + lo (u < PER) of list li, of c entries
+  auto take = [&](int64_t li, uint32_t c, uint32_t p0, int ll, int lo) {
+    int2 ce[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const uint32_t pos = p0 + (uint32_t)(u * ll + lo);
+      ce[u] = make_int2(0, 0);
+      if (pos < c) ce[u] = cand[ilv ? ilv_index(li, pos, (int64_t)nq * S) : li * cap + pos];
+    }
+    uint32_t in = 0u, nin = 0u;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const bool v = p0 + (uint32_t)(u * ll + lo) < c;
+      const float sc = __int_as_float(ce[u].y);
+      const int b = bin_of(bin_x(sc, p.delta, p.c), m);
+      const bool i1 = v & (b >= tau);
+      in |= (uint32_t)i1 << u;
+      nin += (uint32_t)__popcll(__ballot(i1));
+      wab += (uint32_t)__popcll(__ballot(v & (b > tau)));
+      if (i1 & (bool)__builtin_isfinite(sc)) {
+        mn = fminf(mn, sc);
+        mx = fmaxf(mx, sc);
+      }
+    }
+    if (nin == 0) return;
+    uint32_t r0 = 0u;
+    if (l == 0) r0 = atomicAdd(&tmp[26], nin);
+    r0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)r0);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const bool i1 = (in >> u) & 1u;
+      const uint64_t mk = __ballot(i1);
+      const uint32_t r = r0 + mbcnt64(mk);
+      if (i1 && r < slots) e2[r] = ce[u];
+      r0 += (uint32_t)__popcll(mk);
+    }
+  };
+  if (S >= 4 * NW) {
+    // whole lists per wave, four at a time (16 lanes on 16 consecutive
+    // positions of each, one 128-byte chunk)
+    constexpr int ll = kWave / 4;
+    const int sub = l / ll, lo = l - sub * ll;
+    for (int s0 = wave * 4; s0 < S; s0 += NW * 4) {
+      const int64_t li = (int64_t)row * S + s0 + sub;
+      const uint32_t c = s0 + sub < S ? min(cnt[li], (uint32_t)cap) : 0u;
+      uint32_t cmax = 0u;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) cmax = max(cmax, (uint32_t)__builtin_amdgcn_readlane((int)c, g * ll));
+      for (uint32_t p0 = 0; p0 < cmax; p0 += (uint32_t)(PER * ll)) take(li, c, p0, ll, lo);
+    }
+  } else {
+    // few lists (at most a wave's lanes), of any lengths: their runs of
+    // PER * 64 entries go round the waves
+    static_assert(4 * NW <= kWave, "one list per lane");
+    const uint32_t cl = l < S ? min(cnt[(int64_t)row * S + l], (uint32_t)cap) : 0u;
+    uint32_t turn = 0;  // runs handed out so far
+    for (int s = 0; s < S; ++s) {
+      const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cl, s);
+      const uint32_t runs = (c + PER * kWave - 1) / (PER * kWave);
+      for (uint32_t r = (uint32_t)(wave - (int)turn) & (NW - 1); r < runs; r += NW)
+        take((int64_t)row * S + s, c, r * (PER * kWave), kWave, l);
+      turn += runs;
+    }
+  }
+  mn = wave_min(mn);
+  mx = wave_max(mx);
+  if (l == 0) {
+    red[wave] = mn;
+    red[NW + wave] = mx;
+    if (wab) atomicAdd(&tmp[27], wab);
+  }
+  __syncthreads();
+  const uint32_t n = tmp[26];
+  if (n > slots) return -1;
+  if (tmp[27] != c_above) return 1;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    mn = fminf(mn, red[w]);
+    mx = fmaxf(mx, red[NW + w]);
+  }
+
+  if (!order_entries<NTH, EPT>(e2, n, mn, mx, bk, NB, off)) return -1;
+  for (int i = tid; i < k; i += NTH) {
+    const bool v = (uint32_t)i < n;
+    const int2 x = v ? e2[i] : make_int2(-1, __float_as_int(-__builtin_inff()));
+    oi[i] = x.x;
+    // keyed rows report canonical scores (a zero as +0, a NaN as the quiet one)
+    const float sc = __int_as_float(x.y);
+    os[i] = keyed && v ? ord_inv(ord_key(sc)) : sc;
+  }
+  return 0;
+}
+
 template <int NTH, int PER>
 __device__ __forceinline__ void select_row(int row, RowParam* params, const uint32_t* cnt, const uint32_t* hist,
                            const int2* cand, int nq, int S, int HS, int cap, int m, int k, int E, uint32_t flags,
@@ -452,6 +580,27 @@ __device__ __forceinline__ void select_row(int row, RowParam* params, const uint
   if (p.tau0 >= 0 && tau < p.tau0) {
     enqueue(5, tau, 0);
     return;
+  }
+
+  // ---- sorted rows: the keys at or above bin tau in one gather ----
+  // (see select_sorted); a row that it does not take goes on
+  // with the steps below
+  const uint32_t nmax = tau >= 0 ? c_above + c_tie : total_c;
+  if (sorted && nmax <= (uint32_t)sort_slots(E)) {
+    const int done = select_sorted<NTH, PER>(row, p, cnt, cand, nq, S, cap, m, k, E, keyed, ilv, tau, c_above, nmax,
+                                             tmp, off, ent, oi, os);
+    if (done >= 0) {
+      if (done == 0 && stats && tid == 0) {
+        int32_t* st = stats + (int64_t)row * LT_ROW_STATS;
+        if (!(flags & kSelSecond)) st[0] = (int32_t)total_c;
+        st[1] = tau;
+        st[2] = (flags & kSelSecond) ? 6 : 0;
+        st[3] = (int32_t)(tmp[26] - tmp[27]);
+      }
+      if (done == 1) enqueue(4, tau, tmp[26] - tmp[27]);
+      return;
+    }
+    __syncthreads();
   }
 
   // ---- 2./3. one pass over the candidates ----
@@ -861,7 +1010,8 @@ hipError_t launch_select(RowParam* params, const uint32_t* cnt, const uint32_t* 
   // over the lists; many rows fill it with narrow ones (measured on MI355X:
   // 256 rows, 33 K candidates each, 1.57 -> 0.79 ms; 4096 rows with 8.7 K,
   // 0.16 ms at 256 threads against 0.37 ms at 1024)
-  if ((flags & kSelIlv) || nq <= kSelFewRows) go(k_select<kSelThreadsWide, kSelPerWide>, kSelThreadsWide);
+  // (and a sort buffer past 4096 entries leaves room for one block per CU)
+  if ((flags & kSelIlv) || nq <= kSelFewRows || E > 4096) go(k_select<kSelThreadsWide, kSelPerWide>, kSelThreadsWide);
   else go(k_select<kSelThreads, kSelPer>, kSelThreads);
   return hipGetLastError();
 }
@@ -879,7 +1029,7 @@ hipError_t launch_select_second(RowParam* params, const uint32_t* cnt, const uin
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(nth), lds, st, params, cnt, hist, cand, nq, S, HS, cap, m, k, E,
                        flags & ~kSelRefilter, out_i, out_s, qctl, queue, rqueue, rflag, stats);
   };
-  if (flags & kSelIlv) go(k_select_second<kSelThreadsWide, kSelPerWide>, kSelThreadsWide);
+  if ((flags & kSelIlv) || E > 4096) go(k_select_second<kSelThreadsWide, kSelPerWide>, kSelThreadsWide);
   else go(k_select_second<kSelThreads, kSelPer>, kSelThreads);
   return hipGetLastError();
 }

@@ -125,6 +125,95 @@ __host__ __device__ __forceinline__ int next_pow2(int n) {
   return p;
 }
 
+// ---------------------------------------------------------------------------
+// Ordering of up to sort_slots(E) (key, score) entries in LDS by the total
+// order, with one distribution pass: a linear map of the score over [mn, mx]
+// into NB buckets (any map that does not decrease with the score will do; NaN
+// and -inf take the lowest), a suffix sum of the bucket counts, and a rank
+// within the bucket by comparing its few keys. Eight barriers and O(1) LDS
+// operations per key for spread scores, where a bitonic sort of 2048 keys
+// takes 66 stages.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kBucketMax = 128;  // a bucket with more keys (many equal scores): not this way
+// A buffer of E 8-byte entries holds the slots and, after them, the buckets.
+__host__ __device__ constexpr int sort_buckets(int E) { return E / 2; }    // 4 bytes each
+__host__ __device__ constexpr int sort_slots(int E) { return E - E / 4; }  // 8 bytes each
+
+// Buckets for n entries: about one per entry, at least one per thread.
+template <int NTH>
+__device__ __forceinline__ int bucket_count(uint32_t n, int E) {
+  return min(sort_buckets(E), max(NTH, next_pow2((int)n)));
+}
+
+// e2[0, n): the entries, n <= NTH * EPT, rewritten in order; mn, mx: the least
+// and greatest finite score (inf, -inf: none), the same in every thread;
+// bk[0, NB): zeroed, NB a multiple of NTH; tmp: NTH / kWave words. All of it
+// made visible by a barrier. Returns false, in every thread and with e2 as it
+// was, when a bucket holds more than kBucketMax entries. Ends with a barrier.
+template <int NTH, int EPT>
+__device__ __forceinline__ bool order_entries(int2* e2, uint32_t n, float mn, float mx, uint32_t* bk, int NB,
+                                              uint32_t* tmp) {
+  const int tid = threadIdx.x;
+  float scale = (float)NB / (mx - mn);
+  if (!(scale > 0.0f) || !__builtin_isfinite(scale)) scale = 0.0f;
+  const float top = (float)(NB - 1);
+  int2 e[EPT];
+  uint32_t bs[EPT];  // bucket << 16 | slot in the bucket, later the place in the order
+#pragma unroll
+  for (int j = 0; j < EPT; ++j) {
+    const uint32_t i = (uint32_t)(tid + j * NTH);
+    if (i < n) {
+      e[j] = e2[i];
+      const float sc = __int_as_float(e[j].y);
+      const float t = fmaxf(fminf((sc - mn) * scale, top), 0.0f);
+      const uint32_t b = scale > 0.0f && sc == sc ? (uint32_t)t : 0u;
+      bs[j] = b << 16 | atomicAdd(&bk[b], 1u);
+    }
+  }
+  __syncthreads();
+  // bk[b]: start of the bucket in descending order << 16 | its count
+  const int Q = NB / NTH;
+  uint32_t sum = 0, big = 0;
+  for (int i = 0; i < Q; ++i) {
+    const uint32_t c = bk[NB - 1 - (tid * Q + i)];
+    sum += c;
+    big = max(big, c);
+  }
+  uint32_t tot;
+  uint32_t at = block_scan_excl<NTH>(sum, tmp, &tot);
+  for (int i = 0; i < Q; ++i) {
+    uint32_t* pb = &bk[NB - 1 - (tid * Q + i)];
+    const uint32_t c = *pb;
+    *pb = at << 16 | c;
+    at += c;
+  }
+  if (__syncthreads_or(big > kBucketMax)) return false;
+#pragma unroll
+  for (int j = 0; j < EPT; ++j)
+    if ((uint32_t)(tid + j * NTH) < n) e2[(bk[bs[j] >> 16] >> 16) + (bs[j] & 0xFFFFu)] = e[j];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < EPT; ++j) {
+    if ((uint32_t)(tid + j * NTH) < n) {
+      const uint32_t w = bk[bs[j] >> 16], s0 = w >> 16, c = w & 0xFFFFu;
+      uint32_t r = s0;
+      const uint64_t me = comp_key(__int_as_float(e[j].y), (uint32_t)e[j].x);
+      if (c > 1)
+        for (uint32_t i = 0; i < c; ++i) {
+          const int2 o = e2[s0 + i];
+          r += comp_key(__int_as_float(o.y), (uint32_t)o.x) > me;
+        }
+      bs[j] = r;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < EPT; ++j)
+    if ((uint32_t)(tid + j * NTH) < n) e2[bs[j]] = e[j];
+  __syncthreads();
+  return true;
+}
+
 // LDS layout of radix_select_row: a 256-bin histogram per wave (up to
 // kRadixWaves waves), their sum, 32 words of exchange, then the sort entries.
 constexpr int kRadixWaves = 8;

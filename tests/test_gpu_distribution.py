@@ -65,3 +65,20 @@ def test_scores_in_filter_shapes(lib, nq, nk, k, kind, sorted_out):
                                                                              visible_start=st))
     gi, gs = gi.cpu().numpy(), gs.cpu().numpy()
     _check(scores, nk, k, offs, starts, gi, gs, sorted_out, sorted({0, 1 % nq, nq // 2, nq - 1}))
+
+
+# candidate lists per row: one, fewer than a block's waves, more, and four
+# times as many (16 waves up to 512 rows, 4 beyond); integer inputs give exact
+# scores with many ties
+@pytest.mark.parametrize("nq,splits", [(9, 1), (9, 3), (9, 17), (9, 64), (520, 2), (520, 5), (520, 16)])
+@pytest.mark.parametrize("k", [50, 2100])
+def test_fused_sorted_rows(lib, nq, splits, k):
+    x = workloads.exact_inputs(nq, 5000, 64, 128, "bf16", seed=nq + splits)
+    d = to_dev(x)
+    gi, gs = lt.indexer_topk(d["q"], d["w"], d["keys"], k, d["offsets"],
+                             options=lt.make_options(sorted_output=True, key_splits=splits))
+    gi, gs = gi.cpu().numpy(), gs.cpu().numpy()
+    rows = [0, nq // 2, nq - 1]
+    ri, rs, _ = oracle_topk(x, "bf16", k, "dsa", rows=rows)
+    for j, t in enumerate(rows):
+        check_row_exact(gi[t], gs[t], ri[j], rs[j], int(x["offsets"][t]), k, True)
