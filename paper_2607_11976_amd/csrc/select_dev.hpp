@@ -215,11 +215,11 @@ __device__ __forceinline__ bool order_entries(int2* e2, uint32_t n, float mn, fl
 }
 
 // LDS layout of radix_select_row: a 256-bin histogram per wave (up to
-// kRadixWaves waves), their sum, 32 words of exchange, then the sort entries.
-constexpr int kRadixWaves = 8;
+// kRadixWaves waves), their sum, 64 words of exchange, then the sort entries.
+constexpr int kRadixWaves = 16;
 constexpr size_t kRadixTot = (size_t)kRadixWaves * 256 * 4;
 constexpr size_t kRadixTmp = kRadixTot + 256 * 4;
-constexpr size_t kRadixEnt = kRadixTmp + 32 * 4;
+constexpr size_t kRadixEnt = kRadixTmp + 64 * 4;
 
 // Sort entries of radix_select_row: the output sort (k of them) and the keys
 // of a digit prefix gathered in LDS once at most this many remain.
@@ -429,7 +429,7 @@ __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k,
   pad = __builtin_amdgcn_readfirstlane((int)pad) != 0;
   uint32_t* hist = reinterpret_cast<uint32_t*>(lds);              // [NW][256]
   uint32_t* tot = reinterpret_cast<uint32_t*>(lds + kRadixTot);   // [256]
-  uint32_t* tmp = reinterpret_cast<uint32_t*>(lds + kRadixTmp);   // [32]
+  uint32_t* tmp = reinterpret_cast<uint32_t*>(lds + kRadixTmp);   // [64]
   uint64_t* ent = reinterpret_cast<uint64_t*>(lds + kRadixEnt);
   const int tid = threadIdx.x, l = lane_id(), wave = tid / kWave;
   uint32_t* hw = hist + wave * 256;
@@ -596,18 +596,18 @@ __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k,
   const uint32_t kstar = prefix, need = remaining;
   if (l == 0) {
     tmp[wave] = gbefore;
-    tmp[8 + wave] = eqw;
+    tmp[32 + wave] = eqw;
   }
   __syncthreads();
   uint32_t g = 0, e = 0, cg = 0, ce = 0;
   for (int w = 0; w < NW; ++w) {
     if (w < wave) {
       g += tmp[w];
-      e += tmp[8 + w];
+      e += tmp[32 + w];
     }
   }
   cg = tmp[wave];
-  ce = tmp[8 + wave];
+  ce = tmp[32 + wave];
   __syncthreads();
   // a key > K* goes after the keys > K* and the taken keys == K* of lower
   // index; a key == K* is taken while fewer than `need` of lower index were

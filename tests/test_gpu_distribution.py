@@ -67,6 +67,19 @@ def test_scores_in_filter_shapes(lib, nq, nk, k, kind, sorted_out):
     _check(scores, nk, k, offs, starts, gi, gs, sorted_out, sorted({0, 1 % nq, nq // 2, nq - 1}))
 
 
+# 256-thread blocks for many short rows, else 1024; k = 2048 and 2049 are the
+# last with 4096 sort entries and the first with more
+@pytest.mark.parametrize("nq,nk,k", [(600, 3000, 100), (600, 16385, 2048), (40, 16384, 2049), (5, 70001, 8192),
+                                     (3, 4097, 4096)])
+@pytest.mark.parametrize("kind", ["normal", "ties", "narrow", "heavy", "infs", "const"])
+def test_radix_rows(lib, nq, nk, k, kind):
+    scores = _rows(kind, nq, nk, seed=nk + k)
+    offs = workloads.causal_offsets(nq, nk)
+    offs[0] = min(nk, k + 1)
+    gi, gs = lt.topk_radix(scores.cuda(), k, nk, torch.from_numpy(offs).cuda(), sorted_output=True)
+    _check(scores, nk, k, offs, None, gi.cpu().numpy(), gs.cpu().numpy(), True, sorted({0, 1, nq - 1}))
+
+
 # candidate lists per row: one, fewer than a block's waves, more, and four
 # times as many (16 waves up to 512 rows, 4 beyond); integer inputs give exact
 # scores with many ties
