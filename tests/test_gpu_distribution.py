@@ -95,3 +95,21 @@ def test_fused_sorted_rows(lib, nq, splits, k):
     ri, rs, _ = oracle_topk(x, "bf16", k, "dsa", rows=rows)
     for j, t in enumerate(rows):
         check_row_exact(gi[t], gs[t], ri[j], rs[j], int(x["offsets"][t]), k, True)
+
+
+# spans around what the bitmap of a wide (2^20 keys and some) and of a narrow
+# block holds, and keys up to the largest index
+@pytest.mark.parametrize("nq,k,group,span,top", [
+    (16, 512, 8, 1 << 20, 1 << 20), (16, 512, 8, 1 << 21, 1 << 21), (16, 512, 8, 1000, 2 ** 31 - 1),
+    (16, 512, 8, 2 ** 31 - 1, 2 ** 31 - 1), (1100, 64, 2, 200000, 300000), (1100, 64, 2, 400000, 400000),
+    (20, 2048, 16, 131072, 131072), (9, 3000, 3, 50000, 50000), (7, 1, 5, 3, 3)])
+def test_union_spans(lib, nq, k, group, span, top):
+    rng = np.random.default_rng(k + group)
+    idx = (top - span + rng.integers(0, span, size=(nq, k))).astype(np.int32)
+    idx[rng.random((nq, k)) < 0.05] = -1
+    idx[0, 0], idx[0, -1] = top - span, top - 1  # the first group's span is exact
+    u, c, m = lt.dsa_union(torch.from_numpy(idx).cuda(), group)
+    ru, rc, rm = orc.dsa_union(idx, group)
+    np.testing.assert_array_equal(c.cpu().numpy(), rc)
+    np.testing.assert_array_equal(u.cpu().numpy(), ru)
+    np.testing.assert_array_equal(m.cpu().numpy().view(np.uint32), rm)
