@@ -31,6 +31,8 @@ constexpr size_t kLdsPerBlock = 160 * 1024;   // gfx950 LDS per workgroup
 constexpr int kSampleBlockScores = 64;      // scores-in sample: runs of 64 consecutive keys
 constexpr int kMinScoresSplitKeys = 16384;  // shortest key split the scores-in entry makes by itself:
 constexpr int kMinScoresSplitK = 32;        // these keys, and this many times k
+constexpr int kPackedRounds = 4;              // blocks per CU aimed at for packed sequences
+constexpr int kPackedCap = 6;                 // shortest candidate lists they get, in k
 constexpr int kMinSharedSplitKeys = 1024;   // shortest key split of the shared-row (wide) scan
 constexpr int kSharedSample = 65536;        // default sample of the shared-row scan (inner product)
 
@@ -191,11 +193,33 @@ Resolved resolve_fused(const lt_options* o, int nq, int nk, int k, int mode, con
       if (blocks * 10 >= rounds * kTargetBlocks * 9) break;
     }
   }
+  auto split_len = [&](int s) {
+    const int per = (nk + s - 1) / s;
+    return std::max(1, (per + sh.keys_per_step - 1) / sh.keys_per_step) * sh.keys_per_step;
+  };
+  if (r.starts && o->key_splits == 0 && o->capacity <= 0 && !r.shared) {
+    // Packed sequences: the tiles see ranges of different lengths, so blocks
+    // of equal splits end at different times; kPackedRounds blocks per CU even
+    // that out (1251 queries of four sequences of 3 to 41 K keys, bf16: 835,
+    // 786, 768, 736 us a call with 2, 3, 6, 8 splits). Within the memory that
+    // the splits of one sequence take, so that a workspace sized without
+    // visible_start serves: their lists are that much shorter, at least
+    // kPackedCap * k entries or the whole split (no more than that passes).
+    const int want = std::min({(kPackedRounds * kTargetBlocks + tiles - 1) / std::max(tiles, 1),
+                               nk / kMinSplitKeys, kMaxAutoSplits});
+    const int64_t per_list = 4 + 4 * (int64_t)r.m;  // count and histogram
+    const int64_t room = S * (8 * (int64_t)r.cap + per_list) - 1024 / std::max(nq, 1) - 8;
+    for (int s = want; s > S; --s) {
+      const int64_t cap = std::min<int64_t>((room - s * per_list) / (8 * (int64_t)s), split_len(s));
+      if (cap < std::min<int64_t>(split_len(s), (int64_t)kPackedCap * k)) continue;
+      S = s;
+      r.cap = (int)cap;
+      break;
+    }
+  }
   r.S = S;
   r.HS = r.shared ? 1 : S;
-  const int per = (nk + S - 1) / S;
-  r.L = ((per + sh.keys_per_step - 1) / sh.keys_per_step) * sh.keys_per_step;
-  if (r.L == 0) r.L = sh.keys_per_step;
+  r.L = split_len(S);
   return r;
 }
 

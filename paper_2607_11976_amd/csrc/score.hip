@@ -1324,7 +1324,41 @@ __global__ __launch_bounds__(C::NTHREADS) void k_sample(ScoreArgs a, const int32
   extern __shared__ __align__(16) uint8_t lds[];
   const int q0 = blockIdx.x * C::QT, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
             qbase = q0 + wave * C::QW;
-  const int kb = blockIdx.y * slice, ke = min(kb + slice, ns);
+  int kb = blockIdx.y * slice, ke = min(kb + slice, ns);
+  if (a.starts) {
+    // sequences packed into one key array: only the sample keys of the block's
+    // own sequences are ever read, so it scores just the span of its slice
+    // that holds them (1251 queries of four sequences: this stage 150 -> 109 us)
+    int* red = reinterpret_cast<int*>(lds);  // [4], before the tiles fill
+    if (threadIdx.x == 0) {
+      red[0] = a.nk;
+      red[1] = 0;
+      red[2] = ke;
+      red[3] = kb;
+    }
+    __syncthreads();
+    if (threadIdx.x < C::QT && q0 + (int)threadIdx.x < a.nq) {
+      const RowRange rr = row_range(a.offs, a.starts, q0 + threadIdx.x, a.nk);
+      if (rr.e > rr.s) {
+        atomicMin(&red[0], rr.s);
+        atomicMax(&red[1], rr.e);
+      }
+    }
+    __syncthreads();
+    const int us = red[0], ue = red[1];
+    for (int i = kb + (int)threadIdx.x; i < ke; i += C::NTHREADS) {
+      const int v = list[i];
+      if (v >= us && v < ue) {
+        atomicMin(&red[2], i);
+        atomicMax(&red[3], i + 1);
+      }
+    }
+    __syncthreads();
+    kb = red[2];
+    ke = red[3];
+    if (kb >= ke) return;  // block-uniform
+    __syncthreads();  // red is read; the tiles may fill
+  }
   WaveQ<C> wq;
   load_q<C>(wq, a, qbase);
   DenseSink<C> sink{samp, ns, qbase, a.nq};
@@ -1385,9 +1419,13 @@ __global__ __launch_bounds__(C::NTHREADS) void k_fused(ScoreArgs a, const RowPar
   }
   __syncthreads();
   if (*anyon == 0) return;  // block-uniform: none of the block's rows is scanned (second pass)
-  // the split's keys within the union of the block's rows' ranges
-  const int kb = max(split * L, *smin);
-  const int ke = min(min(split * L + L, a.nk), *emax);
+  // the split's share (at most L keys) of the union of the block's rows'
+  // ranges: equal parts, so that the splits of a short sequence packed into a
+  // long key array all have work
+  const int us = *smin, ue = max(*emax, us);
+  const int part = min(L, ((ue - us + S - 1) / S + C::KT - 1) / C::KT * C::KT);
+  const int kb = us + min(split * part, ue - us);
+  const int ke = min(kb + part, ue);
   WaveQ<C> wq;
   load_q<C>(wq, a, qbase);
   std::conditional_t<C::GROUPED, GroupedSink<C>, FusedSink<C>> sink;
@@ -1622,7 +1660,9 @@ hipError_t launch_sample_scores(const ScoreArgs& a, const int32_t* list, int ns,
     // few query tiles (a short chunk): cut the sample into more slices so
     // that the launch still covers the GPU
     const int tiles = (a.nq + C::QT - 1) / C::QT;
-    const int want = tiles > 0 ? (kSampleBlocks + tiles - 1) / tiles : 1;
+    // (and for packed sequences, whose blocks score parts of their slices)
+    const int blocks = kSampleBlocks * (a.starts ? 4 : 1);
+    const int want = tiles > 0 ? (blocks + tiles - 1) / tiles : 1;
     int slice = (ns + want - 1) / want;
     slice = ((slice + C::KT - 1) / C::KT) * C::KT;
     slice = slice < C::KT ? C::KT : (slice > kSlice ? kSlice : slice);
