@@ -375,7 +375,10 @@ int lt_indexer_topk(const void* q, const float* q_scale, const float* w, const v
   if ((e = make_list(r, nk, 1, list, st)) != hipSuccess) return hip_status(e);
   if (r.ns > 0 && (e = launch_sample_scores(a, list, r.ns, samp, st)) != hipSuccess) return hip_status(e);
   record(r, LT_STAGE_RANGE, st);
-  if ((e = launch_range(false, samp, r.ns, nq, nk, offs, r.starts, list, r.ns, r.m, k, params, r.stats, rflag,
+  // without ranges every row sees every key of the random sample (a caller's
+  // list may hold holes)
+  const int32_t* range_list = offs || r.starts || r.keys_in ? list : nullptr;
+  if ((e = launch_range(false, samp, r.ns, nq, nk, offs, r.starts, range_list, r.ns, r.m, k, params, r.stats, rflag,
                         st)) != hipSuccess)
     return hip_status(e);
   record(r, LT_STAGE_FILTER, st);

@@ -22,7 +22,8 @@ __global__ void k_init(uint32_t* qctl) {
 // with the sample's histogram. The sample histogram is NOT carried into the
 // scan: every sampled key is scanned again, and counting it twice could
 // raise the threshold above the true k-th score.
-// The sample is the key list `list` (holes < 0 skipped). FROM_SCORES: its
+// The sample is the key list `list` (holes < 0 skipped; NULL: every sample key
+// is visible to every row, and the list need not be read). FROM_SCORES: its
 // scores are read from a score matrix (scores-in entry); otherwise from the
 // [nq, ns] matrix of sample scores the sample kernel wrote. Each thread keeps
 // kRangeUnroll loads in flight: the kernel is bound by load latency.
@@ -31,6 +32,8 @@ constexpr int kRangeThreads = 256;
 constexpr int kRangeThreadsLarge = 1024;  // samples of kRangeLargeSample keys or more, or few rows
 constexpr int kRangeLargeSample = 16384;
 constexpr int kRangeUnroll = 8;
+constexpr int kRangeThreadsMid = 512;  // two blocks of them fit a CU with kRangeHold * 2 scores a thread
+constexpr int kRangeHold = 32, kRangeHoldFew = 8;  // sample scores a thread keeps in registers
 
 template <int NTH, bool FROM_SCORES>
 __device__ __forceinline__ void range_load(const float* rp, const int32_t* list, int ns, RowRange rr, int base,
@@ -39,7 +42,8 @@ __device__ __forceinline__ void range_load(const float* rp, const int32_t* list,
 #pragma unroll
   for (int u = 0; u < kRangeUnroll; ++u) {
     const int i = base + u * NTH + (int)threadIdx.x;
-    key[u] = i < ns ? list[i] : -1;
+    key[u] = -1;
+    if (i < ns) key[u] = list ? list[i] : rr.s;
   }
 #pragma unroll
   for (int u = 0; u < kRangeUnroll; ++u) {
@@ -49,12 +53,17 @@ __device__ __forceinline__ void range_load(const float* rp, const int32_t* list,
   }
 }
 
-template <int NTH, bool FROM_SCORES>
+// HOLD: sample scores per thread kept in registers (ns <= NTH * HOLD), or 0:
+// read twice. The histogram takes only what tau0 needs of it: the bins from
+// 3m/4 up where they hold k sample keys, else from m/2 up, else all (LDS
+// atomics on the few bins that most scores fall in cost more than the reads).
+template <int NTH, bool FROM_SCORES, int HOLD>
 __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride, int nq, int nk,
                                                          const int32_t* offs, const int32_t* starts,
                                                          const int32_t* list, int ns, int m, int k,
                                                          RowParam* params, int32_t* stats, int32_t* rflag) {
-  constexpr int NW = NTH / kWave;
+  constexpr int NW = NTH / kWave, U = kRangeUnroll, STEP = NTH * U;
+  static_assert(HOLD % U == 0, "whole steps");
   __shared__ uint32_t hist[kMaxBins];
   __shared__ float red_mn[NW], red_mx[NW];
   __shared__ uint32_t red_n[NW];
@@ -64,27 +73,72 @@ __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride,
   const float* rp = src + (int64_t)row * stride;
 
   for (int b = threadIdx.x; b < kMaxBins; b += NTH) hist[b] = 0u;
+  if (threadIdx.x < 2) sel[threadIdx.x] = 0u;
   // the row's flags of the second filter pass (rflag[row]) and of the dense
   // fallback (rflag[nq + row])
   if (rflag && threadIdx.x == 0) {
     rflag[row] = 0;
     rflag[nq + row] = 0;
   }
-  float mn = __builtin_inff(), mx = -__builtin_inff();
+  // step j of the sample: its visible scores, NaN for the others and past ns
+  // (a NaN score is counted as visible and otherwise left out too)
   uint32_t nvis = 0;
-  for (int base = 0; base < ns; base += NTH * kRangeUnroll) {
-    float s[kRangeUnroll];
-    bool vis[kRangeUnroll];
+  auto fetch = [&](int base, float* v, bool count) {
+    float s[U];
+    bool vis[U];
     range_load<NTH, FROM_SCORES>(rp, list, ns, rr, base, s, vis);
 #pragma unroll
-    for (int u = 0; u < kRangeUnroll; ++u) {
-      nvis += vis[u];
-      if (vis[u] && __builtin_isfinite(s[u])) {
-        mn = fminf(mn, s[u]);
-        mx = fmaxf(mx, s[u]);
+    for (int u = 0; u < U; ++u) {
+      if (count) nvis += vis[u];
+      v[u] = vis[u] ? s[u] : __builtin_nanf("");
+    }
+  };
+  constexpr int KEEP = HOLD > 0 ? HOLD : U;
+  float v[KEEP];
+  // every sample key visible: the whole row's loads go out at once, through a
+  // descriptor whose range check needs no branch
+  bool held = false;
+  if constexpr (HOLD > 0 && !FROM_SCORES) {
+    if (!list) {
+      held = true;
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)rp, 0, ns * 4, kBufferRaw);
+#pragma unroll
+      for (int j = 0; j < HOLD; ++j)
+        v[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)threadIdx.x * 4 + j * NTH * 4, 0, 0));
+#pragma unroll
+      for (int j = 0; j < HOLD; ++j) {
+        const bool in = (int)threadIdx.x + j * NTH < ns;
+        nvis += in;
+        v[j] = in ? v[j] : __builtin_nanf("");
       }
     }
   }
+  auto each = [&](bool first, auto&& body) {
+    if constexpr (HOLD > 0) {
+#pragma unroll
+      for (int j = 0; j < HOLD; j += U) {
+        if (j * NTH < ns) {
+          if (first && !held) fetch(j * NTH, v + j, true);
+          body(v + j);
+        }
+      }
+    } else {
+      for (int base = 0; base < ns; base += STEP) {
+        fetch(base, v, first);
+        body(v);
+      }
+    }
+  };
+  float mn = __builtin_inff(), mx = -__builtin_inff();
+  each(true, [&](const float* x) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (__builtin_isfinite(x[u])) {
+        mn = fminf(mn, x[u]);
+        mx = fmaxf(mx, x[u]);
+      }
+    }
+  });
   mn = wave_min(mn);
   mx = wave_max(mx);
   nvis = wave_sum(nvis);
@@ -109,16 +163,35 @@ __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride,
   if (__builtin_isfinite(mn)) c = -mn * delta;
   if (!__builtin_isfinite(c)) c = 0.0f;
 
-  for (int base = 0; base < ns; base += NTH * kRangeUnroll) {
-    float s[kRangeUnroll];
-    bool vis[kRangeUnroll];
-    range_load<NTH, FROM_SCORES>(rp, list, ns, rr, base, s, vis);
+  // the lowest bin that the histogram takes
+  int from = 0;
+  if constexpr (HOLD > 0) {
+    const float hi = (float)(m - m / 4), mid = (float)(m / 2);
+    uint32_t n_hi = 0, n_mid = 0;
+    each(false, [&](const float* x) {
 #pragma unroll
-    for (int u = 0; u < kRangeUnroll; ++u) {
-      const int b = bin_of(bin_x(s[u], delta, c), m);
-      if (vis[u] && b >= 0) atomicAdd(&hist[b], 1u);
+      for (int u = 0; u < U; ++u) {
+        const float t = bin_x(x[u], delta, c);
+        n_hi += t >= hi;
+        n_mid += t >= mid;
+      }
+    });
+    n_hi = wave_sum(n_hi);
+    n_mid = wave_sum(n_mid);
+    if (l == 0) {
+      atomicAdd(&sel[0], n_hi);
+      atomicAdd(&sel[1], n_mid);
     }
+    __syncthreads();
+    from = sel[0] >= (uint32_t)k ? m - m / 4 : sel[1] >= (uint32_t)k ? m / 2 : 0;
   }
+  each(false, [&](const float* x) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int b = bin_of(bin_x(x[u], delta, c), m);
+      if (b >= from) atomicAdd(&hist[b], 1u);
+    }
+  });
   __syncthreads();
   if (wave == 0) {
     const int tau0 = wave_threshold(hist, m, (uint32_t)k, nullptr);
@@ -342,6 +415,8 @@ constexpr int kSecondSelectGrid = 512;  // blocks of the second select (persiste
 // sorted.
 constexpr int kRankMax = 512;
 
+constexpr int kHistUnroll = 8;  // split histograms a thread reads at once
+
 // LDS byte offset of the sort entries of k_select with NTH threads.
 constexpr size_t select_ent_offset(int nth) { return ((size_t)kMaxBins + 32 + nth + 16) * 4; }
 
@@ -528,11 +603,32 @@ __device__ __forceinline__ void select_row(int row, RowParam* params, const uint
   }
 
   // ---- 1. final threshold bin ----
-  for (int b = tid; b < kMaxBins; b += NTH) {
+  // The sum of the row's HS histograms: thread (b, g) adds every
+  // (NTH / kMaxBins)-th of them, kHistUnroll loads in flight (a row of a few
+  // queries has up to 256: one load after the other, 64 and 256 splits of two
+  // rows took 40 and 84 us in this kernel).
+  {
+    constexpr int G = NTH / kMaxBins;
+    static_assert(G >= 1, "one thread per bin at least");
+    const int b = tid & (kMaxBins - 1), g = tid / kMaxBins;
+    const uint32_t* hp = hist + (int64_t)row * HS * m + b;
     uint32_t h = 0;
-    if (b < m)
-      for (int s = 0; s < HS; ++s) h += hist[((int64_t)row * HS + s) * m + b];
-    hsum[b] = h;
+    if (b < m) {
+      for (int s = g; s < HS; s += kHistUnroll * G) {
+        uint32_t x[kHistUnroll];
+#pragma unroll
+        for (int u = 0; u < kHistUnroll; ++u) x[u] = s + u * G < HS ? hp[(int64_t)(s + u * G) * m] : 0u;
+#pragma unroll
+        for (int u = 0; u < kHistUnroll; ++u) h += x[u];
+      }
+    }
+    if constexpr (G == 1) {
+      hsum[b] = h;
+    } else {
+      if (g == 0) hsum[b] = 0u;
+      __syncthreads();
+      if (h) atomicAdd(&hsum[b], h);
+    }
   }
   __syncthreads();
   if (tid < kWave) {
@@ -1159,13 +1255,18 @@ hipError_t launch_range(bool from_scores, const float* src, int64_t stride, int 
   // so are the rows of a launch of few rows, which otherwise leaves most of
   // the GPU idle
   const bool large = ns >= kRangeLargeSample || nq <= kSelFewRows;
-  if (from_scores) {
-    if (large) go(k_range<kRangeThreadsLarge, true>, kRangeThreadsLarge);
-    else go(k_range<kRangeThreads, true>, kRangeThreads);
-  } else {
-    if (large) go(k_range<kRangeThreadsLarge, false>, kRangeThreadsLarge);
-    else go(k_range<kRangeThreads, false>, kRangeThreads);
-  }
+  auto by_size = [&](auto FROM) {
+    constexpr bool F = decltype(FROM)::value;
+    if (!large && ns <= kRangeThreads * kRangeHold) go(k_range<kRangeThreads, F, kRangeHold>, kRangeThreads);
+    else if (!large) go(k_range<kRangeThreads, F, 0>, kRangeThreads);
+    else if (ns <= kRangeThreadsLarge * kRangeHoldFew) go(k_range<kRangeThreadsLarge, F, kRangeHoldFew>, kRangeThreadsLarge);
+    else if (nq > kSelFewRows && ns <= kRangeThreadsMid * 2 * kRangeHold) go(k_range<kRangeThreadsMid, F, 2 * kRangeHold>, kRangeThreadsMid);
+    else if (ns <= kRangeThreadsLarge * kRangeHold) go(k_range<kRangeThreadsLarge, F, kRangeHold>, kRangeThreadsLarge);
+    else if (ns <= kRangeThreadsLarge * 2 * kRangeHold) go(k_range<kRangeThreadsLarge, F, 2 * kRangeHold>, kRangeThreadsLarge);
+    else go(k_range<kRangeThreadsLarge, F, 0>, kRangeThreadsLarge);
+  };
+  if (from_scores) by_size(std::true_type{});
+  else by_size(std::false_type{});
   return hipGetLastError();
 }
 
