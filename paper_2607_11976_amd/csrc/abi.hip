@@ -31,6 +31,7 @@ constexpr size_t kLdsPerBlock = 160 * 1024;   // gfx950 LDS per workgroup
 constexpr int kSampleBlockScores = 64;      // scores-in sample: runs of 64 consecutive keys
 constexpr int kMinScoresSplitKeys = 16384;  // shortest key split the scores-in entry makes by itself:
 constexpr int kMinScoresSplitK = 32;        // these keys, and this many times k
+constexpr int kFillKeys = 256;                // shortest key split made to fill the GPU (64 heads)
 constexpr int kPackedRounds = 4;              // blocks per CU aimed at for packed sequences
 constexpr int kPackedCap = 6;                 // shortest candidate lists they get, in k
 constexpr int kMinSharedSplitKeys = 1024;   // shortest key split of the shared-row (wide) scan
@@ -197,21 +198,31 @@ Resolved resolve_fused(const lt_options* o, int nq, int nk, int k, int mode, con
     const int per = (nk + s - 1) / s;
     return std::max(1, (per + sh.keys_per_step - 1) / sh.keys_per_step) * sh.keys_per_step;
   };
-  if (r.starts && o->key_splits == 0 && o->capacity <= 0 && !r.shared) {
-    // Packed sequences: the tiles see ranges of different lengths, so blocks
-    // of equal splits end at different times; kPackedRounds blocks per CU even
-    // that out (1251 queries of four sequences of 3 to 41 K keys, bf16: 835,
-    // 786, 768, 736 us a call with 2, 3, 6, 8 splits). Within the memory that
-    // the splits of one sequence take, so that a workspace sized without
-    // visible_start serves: their lists are that much shorter, at least
-    // kPackedCap * k entries or the whole split (no more than that passes).
-    const int want = std::min({(kPackedRounds * kTargetBlocks + tiles - 1) / std::max(tiles, 1),
-                               nk / kMinSplitKeys, kMaxAutoSplits});
+  if (o->key_splits == 0 && o->capacity <= 0 && !r.shared && (r.starts || 2 * tiles * S <= kTargetBlocks)) {
+    // More splits, within the memory that these take (so a workspace sized
+    // without visible_start serves, and no shape outgrows the static one),
+    // their lists that much shorter:
+    // * packed sequences: the tiles see ranges of different lengths, so blocks
+    //   of equal splits end at different times; kPackedRounds blocks per CU
+    //   even that out (1251 queries of four sequences of 3 to 41 K keys, bf16:
+    //   835, 786, 768, 736 us a call with 2, 3, 6, 8 splits). Lists of
+    //   kPackedCap * k entries at least, or the whole split.
+    // * launches that leave half of the CUs idle or more: a block per CU, down
+    //   to splits of kFillKeys keys (the grouped scans: one tile). Their lists
+    //   hold the whole split. 64 queries of 4096 float32 keys: 117, 78, 70,
+    //   63 us a call with 8, 16, 32, 64 splits; 2 queries of 100003 fp8 keys:
+    //   75, 69, 66, 67 with 64, 128, 192, 256. (From 192 blocks to 255, 20
+    //   queries of 800000 keys: 653 -> 683 us, for the shorter splits keep
+    //   more candidates.)
+    const int fill_keys = sh.arrival_order ? sh.keys_per_step : kFillKeys;
+    const int want = r.starts ? std::min({(kPackedRounds * kTargetBlocks + tiles - 1) / std::max(tiles, 1),
+                                          nk / kMinSplitKeys, kMaxAutoSplits})
+                              : std::min(kTargetBlocks / std::max(tiles, 1), nk / fill_keys);
     const int64_t per_list = 4 + 4 * (int64_t)r.m;  // count and histogram
     const int64_t room = S * (8 * (int64_t)r.cap + per_list) - 1024 / std::max(nq, 1) - 8;
     for (int s = want; s > S; --s) {
       const int64_t cap = std::min<int64_t>((room - s * per_list) / (8 * (int64_t)s), split_len(s));
-      if (cap < std::min<int64_t>(split_len(s), (int64_t)kPackedCap * k)) continue;
+      if (cap < split_len(s) && (!r.starts || cap < (int64_t)kPackedCap * k)) continue;
       S = s;
       r.cap = (int)cap;
       break;
@@ -252,10 +263,12 @@ inline bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? LT_OK : LT_EHIP; }
 
-// The launch's sample list: the caller's, cleaned, or the random one.
-hipError_t make_list(const Resolved& r, int nk, int blk, int32_t* list, hipStream_t st) {
-  if (r.keys_in) return launch_list_clean(r.keys_in, r.ns, nk, list, st);
-  return launch_sample_list(list, r.ns, nk, blk, r.seed, st);
+// The launch's sample list: the caller's, cleaned, or the random one. The
+// same launch zeroes the queue control words.
+hipError_t make_list(const Resolved& r, int nk, int blk, int32_t* list, uint32_t* qctl, hipStream_t st) {
+  if (r.ns <= 0) return launch_init(qctl, st);
+  if (r.keys_in) return launch_list_clean(r.keys_in, r.ns, nk, list, qctl, st);
+  return launch_sample_list(list, r.ns, nk, blk, r.seed, qctl, st);
 }
 
 inline void record(const Resolved& r, int i, hipStream_t st) {
@@ -371,34 +384,36 @@ int lt_indexer_topk(const void* q, const float* q_scale, const float* w, const v
 
   hipError_t e;
   record(r, LT_STAGE_SAMPLE, st);
-  if ((e = launch_init(qctl, st)) != hipSuccess) return hip_status(e);
-  if ((e = make_list(r, nk, 1, list, st)) != hipSuccess) return hip_status(e);
+  if ((e = make_list(r, nk, 1, list, qctl, st)) != hipSuccess) return hip_status(e);
   if (r.ns > 0 && (e = launch_sample_scores(a, list, r.ns, samp, st)) != hipSuccess) return hip_status(e);
   record(r, LT_STAGE_RANGE, st);
   // without ranges every row sees every key of the random sample (a caller's
   // list may hold holes)
+  // (the bins that the key splits of a row share, where they do)
+  uint64_t* pub = sh.arrival_order && !r.shared && splits_share(r.S) ? reinterpret_cast<uint64_t*>(gate) : nullptr;
   const int32_t* range_list = offs || r.starts || r.keys_in ? list : nullptr;
   if ((e = launch_range(false, samp, r.ns, nq, nk, offs, r.starts, range_list, r.ns, r.m, k, params, r.stats, rflag,
-                        st)) != hipSuccess)
+                        pub, st)) != hipSuccess)
     return hip_status(e);
   record(r, LT_STAGE_FILTER, st);
   e = r.shared ? launch_wide_fused(a, params, r.S, r.L, r.cap, r.m, k, gate, cnt, hist, cand, st)
-               : launch_fused_scan(a, params, r.S, r.L, r.cap, r.m, k, gate, cnt, hist, cand, nullptr, nullptr, st);
+               : launch_fused_scan(a, params, r.S, r.L, r.cap, r.m, k, pub, cnt, hist, cand, nullptr, nullptr, st);
   if (e != hipSuccess) return hip_status(e);
   record(r, LT_STAGE_SELECT, st);
   // lists in arrival order: ties by key, every row sorted (also the rows the
   // fallback completes). Overflowed rows of the one-list-per-split scans get
   // a second filter pass at their final bin before any dense fallback.
-  const bool refilter = !r.shared;
+  // (lists that hold a whole split cannot overflow).
+  const bool refilter = !r.shared && r.cap < r.L;
   const uint32_t sel_flags = r.flags | (sh.arrival_order ? kSelKeyed : 0u) | (r.shared ? kSelIlv : 0u) |
                              (refilter ? kSelRefilter : 0u);
   const uint32_t fb_flags = r.flags | (sh.arrival_order ? LT_SORTED_OUTPUT : 0u);
   if ((e = launch_select(params, cnt, hist, cand, nq, r.S, r.HS, r.cap, r.m, k, r.E, sel_flags, out_idx, out_scores,
-                         qctl, queue, rqueue, rflag, r.stats, st)) != hipSuccess)
+                         qctl, queue, rqueue, rflag, pub, r.stats, st)) != hipSuccess)
     return hip_status(e);
   record(r, LT_STAGE_FALLBACK, st);
   if (refilter) {
-    if ((e = launch_fused_scan(a, params, r.S, r.L, r.cap, r.m, k, gate, cnt, hist, cand, rflag, qctl, st)) !=
+    if ((e = launch_fused_scan(a, params, r.S, r.L, r.cap, r.m, k, pub, cnt, hist, cand, rflag, qctl, st)) !=
         hipSuccess)
       return hip_status(e);
     if ((e = launch_select_second(params, cnt, hist, cand, nq, r.S, r.HS, r.cap, r.m, k, r.E, sel_flags, out_idx,
@@ -489,11 +504,10 @@ int lt_topk_select(const float* scores, int64_t stride, int32_t nq, int32_t nk, 
 
   hipError_t e;
   record(r, LT_STAGE_SAMPLE, st);
-  if ((e = launch_init(qctl, st)) != hipSuccess) return hip_status(e);
-  if ((e = make_list(r, nk, kSampleBlockScores, list, st)) != hipSuccess) return hip_status(e);
+  if ((e = make_list(r, nk, kSampleBlockScores, list, qctl, st)) != hipSuccess) return hip_status(e);
   record(r, LT_STAGE_RANGE, st);
   if ((e = launch_range(true, scores, stride, nq, nk, offs, r.starts, list, r.ns, r.m, k, params, r.stats, nullptr,
-                        st)) != hipSuccess)
+                        nullptr, st)) != hipSuccess)
     return hip_status(e);
   record(r, LT_STAGE_FILTER, st);
   if ((e = launch_filter(scores, stride, nq, nk, offs, r.starts, params, r.S, r.L, r.cap, r.m, k, cnt, hist, cand,
@@ -501,7 +515,7 @@ int lt_topk_select(const float* scores, int64_t stride, int32_t nq, int32_t nk, 
     return hip_status(e);
   record(r, LT_STAGE_SELECT, st);
   if ((e = launch_select(params, cnt, hist, cand, nq, r.S, r.HS, r.cap, r.m, k, r.E, r.flags, out_idx, out_scores, qctl,
-                         queue, nullptr, nullptr, r.stats, st)) != hipSuccess)
+                         queue, nullptr, nullptr, nullptr, r.stats, st)) != hipSuccess)
     return hip_status(e);
   record(r, LT_STAGE_FALLBACK, st);
   if ((e = launch_fallback_scores(scores, stride, nk, offs, r.starts, k, r.flags, qctl, queue, fbc_idx, fbc_score,

@@ -117,6 +117,13 @@ __device__ __forceinline__ float gate_thr(int tau) {
   return tau >= 0 ? (float)tau : -__builtin_inff();
 }
 
+// The published bins of a row's key splits, all at bin tau (-1 = none): a byte
+// each, the bin + 1, bins above 254 as 254 (a lower bin is still a lower
+// bound).
+__device__ __forceinline__ uint64_t pub_word(int tau) {
+  return 0x0101010101010101ull * (uint64_t)(uint8_t)((tau < 254 ? tau : 254) + 1);
+}
+
 // ---------------------------------------------------------------------------
 // Wave-level helpers
 // ---------------------------------------------------------------------------

@@ -19,9 +19,12 @@ hipError_t launch_init(uint32_t* qctl, hipStream_t st);
 // rflag (or NULL): [2 * nq] per-row flags, cleared here: [0, nq) the second
 // filter pass, [nq, 2 nq) the dense fallback (set by the select when it
 // queues a row there).
+// pub (or NULL) [nq]: the bins that the row's key splits publish to each other
+// in the grouped scans, one byte per split (splits_share), preset to the
+// sample's initial bin (pub_word).
 hipError_t launch_range(bool from_scores, const float* src, int64_t stride, int nq, int nk,
                         const int32_t* offs, const int32_t* starts, const int32_t* list, int ns, int m, int k,
-                        RowParam* params, int32_t* stats, int32_t* rflag, hipStream_t st);
+                        RowParam* params, int32_t* stats, int32_t* rflag, uint64_t* pub, hipStream_t st);
 hipError_t launch_filter(const float* scores, int64_t stride, int nq, int nk, const int32_t* offs,
                          const int32_t* starts, const RowParam* params, int S, int L, int cap, int m, int k,
                          uint32_t* cnt, uint32_t* hist, int2* cand, hipStream_t st);
@@ -30,11 +33,12 @@ size_t select_lds_bytes(int E);
 // per row (hist [nq, HS, m]), HS = S or 1.
 // Rows that need the dense fallback go to queue (count qctl[0]); with
 // kSelRefilter in flags, overflowed rows whose final bins fit go to rqueue
-// (count qctl[1]) with rflag set and params[row].tau0 = their final bin.
+// (count qctl[1]) with rflag set, params[row].tau0 = their final bin and, where
+// the splits share thresholds, pub[row] preset to it.
 hipError_t launch_select(RowParam* params, const uint32_t* cnt, const uint32_t* hist, const int2* cand, int nq,
                          int S, int HS, int cap, int m, int k, int E, uint32_t flags, int32_t* out_i, float* out_s,
-                         uint32_t* qctl, int32_t* queue, int32_t* rqueue, int32_t* rflag, int32_t* stats,
-                         hipStream_t st);
+                         uint32_t* qctl, int32_t* queue, int32_t* rqueue, int32_t* rflag, uint64_t* pub,
+                         int32_t* stats, hipStream_t st);
 // The select of the rows in rqueue after their second filter pass.
 hipError_t launch_select_second(RowParam* params, const uint32_t* cnt, const uint32_t* hist, const int2* cand,
                                 int nq, int S, int HS, int cap, int m, int k, int E, uint32_t flags, int32_t* out_i,
@@ -56,9 +60,10 @@ hipError_t launch_radix(const float* scores, int64_t stride, int nq, int nk, con
 
 // ---- sample lists (sample.hip) ----
 // list[i] = the i-th key of the stratified random sample (runs of blk keys).
-hipError_t launch_sample_list(int32_t* list, int ns, int nk, int blk, uint64_t seed, hipStream_t st);
+// qctl [kQctlWords] is zeroed by the same launch (ns >= 1; here and below).
+hipError_t launch_sample_list(int32_t* list, int ns, int nk, int blk, uint64_t seed, uint32_t* qctl, hipStream_t st);
 // out = the caller's list with out-of-range and repeated keys replaced by -1 (ns <= LT_SAMPLE_LIST_MAX).
-hipError_t launch_list_clean(const int32_t* in, int ns, int nk, int32_t* out, hipStream_t st);
+hipError_t launch_list_clean(const int32_t* in, int ns, int nk, int32_t* out, uint32_t* qctl, hipStream_t st);
 // The previous-chunk sample (lt_sample_from_topk); ws holds freq_workspace_bytes(nk).
 size_t freq_workspace_bytes(int nk);
 hipError_t launch_sample_from_topk(const int32_t* prev, int64_t ld, int rows, int pk, int nk, int ns,
@@ -99,13 +104,12 @@ hipError_t launch_sample_scores(const ScoreArgs& a, const int32_t* list, int ns,
 // Dense scores: out[t * ld + s] = I(t, s) for every key.
 hipError_t launch_dense_scores(const ScoreArgs& a, float* out, int64_t ld, hipStream_t st);
 // Fused score + gate + write-back scan over S key splits of L keys each;
-// pub [nq * 8 bytes] holds the bins the splits of each row publish where they
-// share thresholds (initialised here).
+// pub [nq] (or NULL): the bins the splits of each row publish (launch_range).
 // rflag NULL: every row. Else the second filter pass: only rows with
 // rflag[t] set are scanned and written (blocks without such rows, and every
 // block when qctl[1] == 0, return at once).
 hipError_t launch_fused_scan(const ScoreArgs& a, const RowParam* params, int S, int L, int cap, int m,
-                             int k, int* pub, uint32_t* cnt, uint32_t* hist, int2* cand, const int32_t* rflag,
+                             int k, uint64_t* pub, uint32_t* cnt, uint32_t* hist, int2* cand, const int32_t* rflag,
                              const uint32_t* qctl, hipStream_t st);
 // Exact fallback for queued rows (queue, length qctl[0]): dense re-score
 // into scratch rows of nk floats (`slots` of them), then radix select. The
@@ -151,11 +155,18 @@ __host__ __device__ inline int fallback_chunks(uint32_t n, int grid, int slots, 
 }
 // Dense mode (see above): any queue the split mode does not take, when every
 // row has a scratch row and the scan's query tiles hold at most 64 rows (the
-// tile's row slots are bytes). kDenseSlice keys per item.
+// tile's row slots are bytes). kDenseSlice keys per item. Calls of at most
+// kMaxSplitRows rows do without it: their queues either split or, over fewer
+// keys than two chunks, take the whole-row mode (one block per row).
 constexpr int kDenseSlice = 8192;
-__host__ __device__ inline bool fallback_dense(uint32_t n, int nq, int grid, int slots, int nk, int qt) {
-  return n > 0 && qt <= 64 && nq <= slots && fallback_chunks(n, grid, slots, nk) == 1;
+__host__ __device__ inline bool may_dense(int nq, int slots, int qt) {
+  return nq > kMaxSplitRows && nq <= slots && qt <= 64;
 }
+__host__ __device__ inline bool fallback_dense(uint32_t n, int nq, int grid, int slots, int nk, int qt) {
+  return n > 0 && may_dense(nq, slots, qt) && fallback_chunks(n, grid, slots, nk) == 1;
+}
+// Key splits of one row that share thresholds through bytes of one word.
+__host__ __device__ inline bool splits_share(int S) { return S > 1 && S <= 8; }
 // cidx / cscore [kFallbackGrid * k]: the split mode's chunk candidates.
 hipError_t launch_fused_fallback(const ScoreArgs& a, int k, uint32_t flags, uint32_t* qctl, const int32_t* queue,
                                  int32_t* fbflag, int batch, int slots, float* scratch, int32_t* cidx, float* cscore,

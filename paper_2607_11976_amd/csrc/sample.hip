@@ -16,14 +16,23 @@
 
 namespace lt {
 
-__global__ __launch_bounds__(256) void k_sample_list(int32_t* list, int ns, int nk, int blk, uint64_t seed) {
+// The queue control words are zeroed along with the list (a kernel, not a
+// memset, so the launch sequence can be captured in a graph).
+__device__ __forceinline__ void zero_qctl(uint32_t* qctl, int nth) {
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < kQctlWords; i += nth) qctl[i] = 0u;
+}
+
+__global__ __launch_bounds__(256) void k_sample_list(int32_t* list, int ns, int nk, int blk, uint64_t seed,
+                                                     uint32_t* qctl) {
+  zero_qctl(qctl, 256);
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < ns) list[i] = sample_key(i, ns, nk, blk, seed);
 }
 
-hipError_t launch_sample_list(int32_t* list, int ns, int nk, int blk, uint64_t seed, hipStream_t st) {
-  if (ns <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_sample_list, dim3((ns + 255) / 256), dim3(256), 0, st, list, ns, nk, blk, seed);
+hipError_t launch_sample_list(int32_t* list, int ns, int nk, int blk, uint64_t seed, uint32_t* qctl,
+                              hipStream_t st) {
+  hipLaunchKernelGGL(k_sample_list, dim3((ns + 255) / 256), dim3(256), 0, st, list, ns, nk, blk, seed, qctl);
   return hipGetLastError();
 }
 
@@ -35,7 +44,9 @@ hipError_t launch_sample_list(int32_t* list, int ns, int nk, int blk, uint64_t s
 // write holes (-1) for everything else.
 constexpr int kCleanThreads = 1024;
 
-__global__ __launch_bounds__(kCleanThreads) void k_list_clean(const int32_t* in, int ns, int nk, int32_t* out) {
+__global__ __launch_bounds__(kCleanThreads) void k_list_clean(const int32_t* in, int ns, int nk, int32_t* out,
+                                                              uint32_t* qctl) {
+  zero_qctl(qctl, kCleanThreads);
   extern __shared__ __align__(16) uint32_t a[];
   __shared__ int wave_last[kCleanThreads / kWave];
   const int tid = threadIdx.x, l = lane_id(), w = tid / kWave;
@@ -85,12 +96,11 @@ __global__ __launch_bounds__(kCleanThreads) void k_list_clean(const int32_t* in,
   }
 }
 
-hipError_t launch_list_clean(const int32_t* in, int ns, int nk, int32_t* out, hipStream_t st) {
-  if (ns <= 0) return hipSuccess;
+hipError_t launch_list_clean(const int32_t* in, int ns, int nk, int32_t* out, uint32_t* qctl, hipStream_t st) {
   const size_t lds = (size_t)next_pow2(ns) * 4;
   if (lds > 65536)
     (void)hipFuncSetAttribute((const void*)k_list_clean, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(k_list_clean, dim3(1), dim3(kCleanThreads), lds, st, in, ns, nk, out);
+  hipLaunchKernelGGL(k_list_clean, dim3(1), dim3(kCleanThreads), lds, st, in, ns, nk, out, qctl);
   return hipGetLastError();
 }
 

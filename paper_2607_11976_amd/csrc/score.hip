@@ -1433,8 +1433,7 @@ __global__ __launch_bounds__(C::NTHREADS) void k_fused(ScoreArgs a, const RowPar
   if constexpr (C::GROUPED) {
     sink.bind(lds + C::SCAN_LDS + wave * GroupedSink<C>::kLdsPerWave);
     sink.kq0 = kb;
-    // splits share thresholds through one byte per (row, split): up to 8 splits
-    sink.pub = S > 1 && S <= 8 ? pub : nullptr;
+    sink.pub = pub;
   }
   sink.cand = cand;
   sink.rflag = rflag;
@@ -1697,14 +1696,8 @@ hipError_t launch_dense_scores(const ScoreArgs& a, float* out, int64_t ld, hipSt
   return err;
 }
 
-// Published bins of the rows' splits start at the sample's (stored + 1).
-__global__ void k_pub_init(const RowParam* params, int nq, uint64_t* pub) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nq; i += (int64_t)gridDim.x * blockDim.x)
-    pub[i] = 0x0101010101010101ull * (uint64_t)(uint8_t)(min(params[i].tau0, 254) + 1);
-}
-
 hipError_t launch_fused_scan(const ScoreArgs& a, const RowParam* params, int S, int L, int cap, int m, int k,
-                             int* pub, uint32_t* cnt, uint32_t* hist, int2* cand, const int32_t* rflag,
+                             uint64_t* pub, uint32_t* cnt, uint32_t* hist, int2* cand, const int32_t* rflag,
                              const uint32_t* qctl, hipStream_t st) {
   hipError_t err = hipErrorInvalidValue;
   with_cfg(a.dtype, a.mode, a.h, a.d, a.w == nullptr, [&]<class C>() {
@@ -1712,11 +1705,6 @@ hipError_t launch_fused_scan(const ScoreArgs& a, const RowParam* params, int S, 
     if (tiles == 0) {
       err = hipSuccess;
       return;
-    }
-    if (C::GROUPED && S > 1 && S <= 8) {
-      hipLaunchKernelGGL(k_pub_init, dim3((a.nq + 255) / 256), dim3(256), 0, st, params, a.nq,
-                         reinterpret_cast<uint64_t*>(pub));
-      if ((err = hipGetLastError()) != hipSuccess) return;
     }
     const size_t lds = C::SCAN_LDS + fused_sink_lds<C>() + (size_t)C::QT * m * 4 + 16;
     if (lds > 65536)

@@ -8,8 +8,8 @@
 namespace lt {
 
 // ---------------------------------------------------------------------------
-// Zero the queue counters, the fallback cursor and its chunk counters (a
-// kernel, not a memset, so the launch sequence can be captured in a graph).
+// Zero the queue counters, the fallback cursor and its chunk counters, where
+// no sample list is made that would do it.
 // ---------------------------------------------------------------------------
 __global__ void k_init(uint32_t* qctl) {
   for (int i = threadIdx.x; i < kQctlWords; i += blockDim.x) qctl[i] = 0u;
@@ -61,7 +61,8 @@ template <int NTH, bool FROM_SCORES, int HOLD>
 __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride, int nq, int nk,
                                                          const int32_t* offs, const int32_t* starts,
                                                          const int32_t* list, int ns, int m, int k,
-                                                         RowParam* params, int32_t* stats, int32_t* rflag) {
+                                                         RowParam* params, int32_t* stats, int32_t* rflag,
+                                                         uint64_t* pub) {
   constexpr int NW = NTH / kWave, U = kRangeUnroll, STEP = NTH * U;
   static_assert(HOLD % U == 0, "whole steps");
   __shared__ uint32_t hist[kMaxBins];
@@ -196,6 +197,7 @@ __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride,
   if (wave == 0) {
     const int tau0 = wave_threshold(hist, m, (uint32_t)k, nullptr);
     if (l == 0) params[row] = RowParam{delta, c, tau0, (int)nvis};
+    if (pub && l == 0) pub[row] = pub_word(tau0);
     if (stats && l == 0) {
       int32_t* sr = stats + (int64_t)row * LT_ROW_STATS;
       sr[4] = tau0;
@@ -552,7 +554,7 @@ template <int NTH, int PER>
 __device__ __forceinline__ void select_row(int row, RowParam* params, const uint32_t* cnt, const uint32_t* hist,
                            const int2* cand, int nq, int S, int HS, int cap, int m, int k, int E, uint32_t flags,
                            int32_t* out_i, float* out_s, uint32_t* qctl, int32_t* queue, int32_t* rqueue,
-                           int32_t* rflag, int32_t* stats) {
+                           int32_t* rflag, uint64_t* pub, int32_t* stats) {
   extern __shared__ __align__(16) uint8_t lds[];
   uint32_t* hsum = reinterpret_cast<uint32_t*>(lds);          // [256]
   uint32_t* tmp = hsum + kMaxBins;                             // [32]
@@ -653,6 +655,7 @@ __device__ __forceinline__ void select_row(int row, RowParam* params, const uint
     if ((flags & kSelRefilter) && tau >= 0 && c_above + c_tie <= (uint32_t)cap && c_tie <= (uint32_t)E) {
       if (tid == 0) {
         params[row].tau0 = tau;
+        if (pub) pub[row] = pub_word(tau);
         rflag[row] = 1;
         rqueue[atomicAdd(&qctl[1], 1u)] = row;
         if (stats) {
@@ -953,9 +956,9 @@ template <int NTH, int PER>
 __global__ __launch_bounds__(NTH) void k_select(
     RowParam* params, const uint32_t* cnt, const uint32_t* hist, const int2* cand, int nq,
     int S, int HS, int cap, int m, int k, int E, uint32_t flags, int32_t* out_i, float* out_s,
-    uint32_t* qctl, int32_t* queue, int32_t* rqueue, int32_t* rflag, int32_t* stats) {
+    uint32_t* qctl, int32_t* queue, int32_t* rqueue, int32_t* rflag, uint64_t* pub, int32_t* stats) {
   select_row<NTH, PER>(blockIdx.x, params, cnt, hist, cand, nq, S, HS, cap, m, k, E, flags, out_i, out_s, qctl,
-                       queue, rqueue, rflag, stats);
+                       queue, rqueue, rflag, pub, stats);
 }
 
 // The rows of the second filter pass (queue rqueue, length qctl[1]);
@@ -968,7 +971,7 @@ __global__ __launch_bounds__(NTH) void k_select_second(
   const uint32_t n = qctl[1];
   for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
     select_row<NTH, PER>(rqueue[i], params, cnt, hist, cand, nq, S, HS, cap, m, k, E, flags | kSelSecond, out_i,
-                         out_s, qctl, queue, rqueue, rflag, stats);
+                         out_s, qctl, queue, rqueue, rflag, nullptr, stats);
     __syncthreads();
   }
 }
@@ -1245,11 +1248,11 @@ hipError_t launch_init(uint32_t* qctl, hipStream_t st) {
 
 hipError_t launch_range(bool from_scores, const float* src, int64_t stride, int nq, int nk,
                         const int32_t* offs, const int32_t* starts, const int32_t* list, int ns, int m, int k,
-                        RowParam* params, int32_t* stats, int32_t* rflag, hipStream_t st) {
+                        RowParam* params, int32_t* stats, int32_t* rflag, uint64_t* pub, hipStream_t st) {
   dim3 grid(nq);
   auto go = [&](auto kernel, int nth) {
     hipLaunchKernelGGL(kernel, grid, dim3(nth), 0, st, src, stride, nq, nk, offs, starts, list, ns, m, k, params,
-                       stats, rflag);
+                       stats, rflag, pub);
   };
   // a long sample is read in fewer, wider steps (the kernel waits on loads);
   // so are the rows of a launch of few rows, which otherwise leaves most of
@@ -1295,13 +1298,13 @@ size_t select_lds_bytes(int E) { return select_ent_offset(kSelThreadsWide) + (si
 
 hipError_t launch_select(RowParam* params, const uint32_t* cnt, const uint32_t* hist, const int2* cand, int nq,
                          int S, int HS, int cap, int m, int k, int E, uint32_t flags, int32_t* out_i, float* out_s,
-                         uint32_t* qctl, int32_t* queue, int32_t* rqueue, int32_t* rflag, int32_t* stats,
-                         hipStream_t st) {
+                         uint32_t* qctl, int32_t* queue, int32_t* rqueue, int32_t* rflag, uint64_t* pub,
+                         int32_t* stats, hipStream_t st) {
   auto go = [&](auto kernel, int nth) {
     const size_t lds = select_ent_offset(nth) + (size_t)E * 8;
     if (lds > 65536) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kernel, dim3(nq), dim3(nth), lds, st, params, cnt, hist, cand, nq, S, HS, cap, m, k, E, flags,
-                       out_i, out_s, qctl, queue, rqueue, rflag, stats);
+                       out_i, out_s, qctl, queue, rqueue, rflag, pub, stats);
   };
   // one block per row: a launch of few rows (a short chunk) fills the GPU
   // only with wide blocks, whose more loads in flight also shorten the walk
@@ -1347,7 +1350,7 @@ hipError_t launch_fallback_scores(const float* scores, int64_t stride, int nk, c
 hipError_t launch_fallback_rows(const uint32_t* qctl, const int32_t* fbflag, const float* scratch, int nq, int nk,
                                 const int32_t* offs, const int32_t* starts, int k, uint32_t flags, int slots,
                                 int qt, int32_t* out_i, float* out_s, hipStream_t st) {
-  if (nq <= 0 || nq > slots || qt > 64) return hipSuccess;  // the dense mode cannot hold
+  if (!may_dense(nq, slots, qt)) return hipSuccess;
   const size_t lds = radix_lds_bytes(k);
   if (lds > 65536)
     (void)hipFuncSetAttribute((const void*)k_fallback_rows, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -97,6 +97,34 @@ def test_fused_sorted_rows(lib, nq, splits, k):
         check_row_exact(gi[t], gs[t], ri[j], rs[j], int(x["offsets"][t]), k, True)
 
 
+# launches of few query tiles: splits down to one key tile, rows whose lists
+# hold a whole split (no second pass), the fallback without its dense mode (up
+# to 128 rows; fewer keys than two chunks: whole rows), and a second pass over
+# splits that share thresholds
+@pytest.mark.parametrize("nq,nk,h,d,dtype,mode,k,opt", [
+    (1, 64, 64, 128, "bf16", "dsa", 5, dict()),
+    (3, 5000, 64, 128, "fp8", "dsa", 700, dict()),
+    (20, 9001, 4, 128, "bf16", "dsa", 300, dict()),
+    (50, 3000, 1, 64, "f32", "ip", 100, dict()),
+    (50, 3000, 1, 64, "f32", "ip", 100, dict(force_fallback=True)),
+    (128, 8191, 64, 128, "bf16", "dsa", 64, dict(force_fallback=True)),
+    (129, 8191, 64, 128, "bf16", "dsa", 64, dict(force_fallback=True)),
+    (40, 20000, 1, 128, "bf16", "ip", 200, dict(key_splits=4, capacity=400)),
+])
+def test_fused_few_tiles(lib, nq, nk, h, d, dtype, mode, k, opt):
+    x = workloads.exact_inputs(nq, nk, h, d, dtype, seed=nq + nk)
+    if mode == "ip":
+        x["w"] = None
+    dev = to_dev(x)
+    gi, gs = lt.indexer_topk(dev["q"], dev["w"], dev["keys"], k, dev["offsets"], dev["q_scale"], dev["k_scale"], mode,
+                             lt.make_options(sorted_output=True, **opt))
+    gi, gs = gi.cpu().numpy(), gs.cpu().numpy()
+    rows = sorted({0, nq // 2, nq - 1})
+    ri, rs, _ = oracle_topk(x, dtype, k, mode, rows=rows)
+    for j, t in enumerate(rows):
+        check_row_exact(gi[t], gs[t], ri[j], rs[j], int(x["offsets"][t]), k, True)
+
+
 # spans around what the bitmap of a wide (2^20 keys and some) and of a narrow
 # block holds, and keys up to the largest index
 @pytest.mark.parametrize("nq,k,group,span,top", [
