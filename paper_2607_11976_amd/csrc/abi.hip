@@ -198,7 +198,7 @@ Resolved resolve_fused(const lt_options* o, int nq, int nk, int k, int mode, con
     const int per = (nk + s - 1) / s;
     return std::max(1, (per + sh.keys_per_step - 1) / sh.keys_per_step) * sh.keys_per_step;
   };
-  if (o->key_splits == 0 && o->capacity <= 0 && !r.shared && (r.starts || 2 * tiles * S <= kTargetBlocks)) {
+  if (o->key_splits == 0 && o->capacity <= 0 && !r.shared && (r.starts || 3 * tiles * S <= 2 * kTargetBlocks)) {
     // More splits, within the memory that these take (so a workspace sized
     // without visible_start serves, and no shape outgrows the static one),
     // their lists that much shorter:
@@ -207,7 +207,7 @@ Resolved resolve_fused(const lt_options* o, int nq, int nk, int k, int mode, con
     //   even that out (1251 queries of four sequences of 3 to 41 K keys, bf16:
     //   835, 786, 768, 736 us a call with 2, 3, 6, 8 splits). Lists of
     //   kPackedCap * k entries at least, or the whole split.
-    // * launches that leave half of the CUs idle or more: a block per CU, down
+    // * launches that leave a third of the CUs idle or more: a block per CU, down
     //   to splits of kFillKeys keys (the grouped scans: one tile). Their lists
     //   hold the whole split. 64 queries of 4096 float32 keys: 117, 78, 70,
     //   63 us a call with 8, 16, 32, 64 splits; 2 queries of 100003 fp8 keys:

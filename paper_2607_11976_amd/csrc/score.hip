@@ -460,23 +460,18 @@ __device__ __forceinline__ uint32_t lds_get1(const uint32_t* p) {
   asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r) : "v"(a) : "memory");
   return r;
 }
-// N (2 or 8) consecutive 16-byte LDS reads under one wait
+// N (1 or 4) consecutive 16-byte LDS reads under one wait
 template <int N>
 __device__ __forceinline__ void lds_get_n(const float* p, f32x4_t (&o)[N]) {
-  static_assert(N == 2 || N == 8, "record sizes of the grouped layouts");
+  static_assert(N == 1 || N == 4, "record sizes of the grouped layouts");
   const uint32_t a = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float*)p;
-  if constexpr (N == 2) {
-    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(o[0]), "=&v"(o[1])
-                 : "v"(a)
-                 : "memory");
+  if constexpr (N == 1) {
+    asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(o[0]) : "v"(a) : "memory");
   } else {
     asm volatile(
-        "ds_read_b128 %0, %8\n\tds_read_b128 %1, %8 offset:16\n\t"
-        "ds_read_b128 %2, %8 offset:32\n\tds_read_b128 %3, %8 offset:48\n\t"
-        "ds_read_b128 %4, %8 offset:64\n\tds_read_b128 %5, %8 offset:80\n\t"
-        "ds_read_b128 %6, %8 offset:96\n\tds_read_b128 %7, %8 offset:112\n\ts_waitcnt lgkmcnt(0)"
-        : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7])
+        "ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:16\n\t"
+        "ds_read_b128 %2, %4 offset:32\n\tds_read_b128 %3, %4 offset:48\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3])
         : "v"(a)
         : "memory");
   }
@@ -529,6 +524,8 @@ template <class C, class Src, class Sink>
 __device__ __forceinline__ void wg_scan(const ScoreArgs& a, const Src& src, int kbeg, int kend, uint8_t* tiles,
                                         const WaveQ<C>& wq, Sink& sink) {
   using Frag = typename C::M::Frag;
+  // sinks that take the scores of one sub-tile at a time
+  constexpr bool kHalves = requires(const float (&x)[C::NIH]) { sink.margin(x); };
   const int tid = threadIdx.x, l = lane_id(), h = l >> 5, r32 = l & 31;
   const uint8_t* keys = static_cast<const uint8_t*>(a.keys);
   // the bounds are the same in every lane; saying so keeps the per-tile
@@ -700,21 +697,42 @@ __device__ __forceinline__ void wg_scan(const ScoreArgs& a, const Src& src, int 
     mma_half<C>(wq, b0, acc0);
     load_b_at<C, SLOT, 1>(tiles, bl, b1);
     reduce_half<C>(wq, acc1, h1);
-    float sc[C::NI];
-    scores(st - 1, h0, h1, sc);
-    schedule_half<C>();
-    // half step B: MFMA sub-tile 1 of tile st || epilogue of sub-tile 0 of st,
-    // B fragments of the next tile's sub-tile 0 read as the slots free up
-    mma_half<C>(wq, b1, acc1);
-    load_b_at<C, (SLOT + 1) & 3, 0>(tiles, bl, b0);
-    reduce_half<C>(wq, acc0, h0);
-    schedule_half<C>();
-    // h0 is only read in the next step; without this use the compiler sinks
-    // its epilogue below the gate's branches, out of the MFMA shadow
+    if constexpr (kHalves) {
+      // the sink takes each sub-tile's scores: their gate, too, runs under the
+      // MFMAs of the other sub-tile (acc and the margin are pinned ahead of
+      // the sink's branch, past which the compiler would move them)
+      const float mx = sink.margin(h1);
+      schedule_half<C>();
 #pragma unroll
-    for (int j = 0; j < C::NIH; ++j) asm volatile("" ::"v"(h0[j]));
-    // gate + write-back of tile st-1 while the last MFMAs drain
-    sink.consume(st - 1, kbeg + (st - 1) * C::KT, kend, sc, st > 0);
+      for (int mt = 0; mt < C::MT; ++mt) asm volatile("" ::"v"(acc0[mt]));
+      asm volatile("" ::"v"(mx));
+      if (st > 0) sink.take(kbeg + (st - 1) * C::KT + 32, 1, h1, mx);
+      mma_half<C>(wq, b1, acc1);
+      load_b_at<C, (SLOT + 1) & 3, 0>(tiles, bl, b0);
+      reduce_half<C>(wq, acc0, h0);
+      const float mx0 = sink.margin(h0);
+      schedule_half<C>();
+#pragma unroll
+      for (int mt = 0; mt < C::MT; ++mt) asm volatile("" ::"v"(acc1[mt]));
+      asm volatile("" ::"v"(mx0));
+      sink.take(kbeg + st * C::KT, 0, h0, mx0);
+    } else {
+      float sc[C::NI];
+      scores(st - 1, h0, h1, sc);
+      schedule_half<C>();
+      // half step B: MFMA sub-tile 1 of tile st || epilogue of sub-tile 0 of st,
+      // B fragments of the next tile's sub-tile 0 read as the slots free up
+      mma_half<C>(wq, b1, acc1);
+      load_b_at<C, (SLOT + 1) & 3, 0>(tiles, bl, b0);
+      reduce_half<C>(wq, acc0, h0);
+      schedule_half<C>();
+      // h0 is only read in the next step; without this use the compiler sinks
+      // its epilogue below the gate's branches, out of the MFMA shadow
+#pragma unroll
+      for (int j = 0; j < C::NIH; ++j) asm volatile("" ::"v"(h0[j]));
+      // gate + write-back of tile st-1 while the last MFMAs drain
+      sink.consume(st - 1, kbeg + (st - 1) * C::KT, kend, sc, st > 0);
+    }
     sync_tiles(1);  // tile st+2 landed; tile st+3 may still be in flight
   };
   using I0 = std::integral_constant<int, 0>;
@@ -732,9 +750,13 @@ __device__ __forceinline__ void wg_scan(const ScoreArgs& a, const Src& src, int 
   if (st < nsteps) body(I1{}, st++);
   if (st < nsteps) body(I2{}, st++);
   reduce_half<C>(wq, acc1, h1);
-  float sc[C::NI];
-  scores(nsteps - 1, h0, h1, sc);
-  sink.consume(nsteps - 1, kbeg + (nsteps - 1) * C::KT, kend, sc, true);
+  if constexpr (kHalves) {
+    sink.take(kbeg + (nsteps - 1) * C::KT + 32, 1, h1, sink.margin(h1));
+  } else {
+    float sc[C::NI];
+    scores(nsteps - 1, h0, h1, sc);
+    sink.consume(nsteps - 1, kbeg + (nsteps - 1) * C::KT, kend, sc, true);
+  }
   sync_tiles(0);  // no prefetch may still be writing LDS when the caller reuses it
 }
 
@@ -939,8 +961,13 @@ struct FusedSink {
 // counted. The order of a list's entries depends on the order in which the
 // atomics are served; the final select orders candidates by (score, key)
 // alone, so no result depends on it.
+// Each 32-key sub-tile is gated on its own (margin, take), while the other
+// sub-tile's MFMAs run: gated together at the end of a tile, nothing of that
+// work was under a MFMA (10000 rows x 4M, k = 100: scan 11.4 -> 10.4 ms; a
+// queue of 64 half-size records where 32 were: 1000 rows x 1M, k = 300, call
+// 2.47 -> 1.14 ms; 16 rows x 3M, k = 1000, 2.52 -> 1.31 ms).
 // Passing scores are not written out in the tile that finds them: every
-// lane with one appends a record of its tile scores to the wave's LDS queue
+// lane with one appends a record of its sub-tile scores to the wave's LDS queue
 // (a ballot, mbcnt for the slot, a few LDS writes, no round trip), and every
 // kDrainEvery tiles all waves drain their queues at once, one record per
 // lane, re-checking each score against its row's current gate.
@@ -976,22 +1003,28 @@ struct GroupedSink {
     int s, e;        // visible keys [s, e) within this split
     int pad;
   };
-  static constexpr int kRecs = 32;        // records of a wave's queue: a lane's scores of one tile
+  static constexpr int kRecs = 64;        // records of a wave's queue: a lane's scores of one sub-tile
+  // lanes of a sub-tile that are queued; of more, the scores are handled in
+  // place. (Queueing those too, in two batches, is faster where most lanes
+  // pass for long -- 2000 rows x 200000, k = 1000: 1.83 -> 1.35 ms -- but the
+  // compiler then moves the gates' registers on the path where nothing passes:
+  // 10000 rows x 4M 11.3 -> 12.3 ms.)
+  static constexpr int kAppend = 56;
   static constexpr int kDrainEvery = 16;  // tiles between queue drains
   static constexpr int kShareEvery = 8;   // tiles between reads of the published bins
   static constexpr int kLdsPerWave =
-      C::QW * (int)sizeof(QState) + 3 * C::QW * 4 + kRecs * C::NI * 4 + ((kRecs * 4 + 15) & ~15);
-  static_assert(C::NI % 4 == 0 && (C::QW * 12) % 16 == 0, "16-byte aligned records");
+      C::QW * (int)sizeof(QState) + 3 * C::QW * 4 + kRecs * C::NIH * 4 + ((kRecs * 4 + 15) & ~15);
+  static_assert(C::NIH % 4 == 0 && (C::QW * 12) % 16 == 0, "16-byte aligned records");
   QState* qs;         // LDS [QW]
   uint32_t* tail;     // LDS [QW]: candidates passed (the list length; may exceed cap)
   uint32_t* above;    // LDS [QW]: counted candidates in bins above tau
   uint32_t* above_s;  // LDS [QW]: the same above tau_s
-  float* rec;         // LDS [kRecs][NI]: a lane's scores of one tile
-  uint32_t* rhdr;     // LDS [kRecs]: (tile's first key - kq0) << 8 | lane
+  float* rec;         // LDS [kRecs][NIH]: a lane's scores of one sub-tile
+  uint32_t* rhdr;     // LDS [kRecs]: (sub-tile's first key - kq0) << 8 | lane
   int qlen;           // records in the queue
   int kq0;            // first key of the split
   bool use_queue;     // keys of the split are told apart by 24 bits
-  float tq[C::NIH];   // T of the query of item j (items j and j + NIH share it)
+  float tq[C::NIH];   // T of the query of item j
   bool ungated;       // some row of the wave has no gate (tau = -1)
   int vis_s, vis_e;   // every row of the wave sees [vis_s, vis_e)
   uint8_t* pub;       // [nq][8] published bins + 1 of the row's splits (2 to 8), or NULL
@@ -1012,7 +1045,7 @@ struct GroupedSink {
     above = tail + C::QW;
     above_s = above + C::QW;
     rec = reinterpret_cast<float*>(above_s + C::QW);
-    rhdr = reinterpret_cast<uint32_t*>(rec + kRecs * C::NI);
+    rhdr = reinterpret_cast<uint32_t*>(rec + kRecs * C::NIH);
   }
 
   __device__ __forceinline__ static float gate_floor(float delta, float c, int tau) {
@@ -1111,43 +1144,49 @@ struct GroupedSink {
     tau_v = t;
   }
 
-  __device__ __forceinline__ void consume(int, int k0, int, const float (&sc)[C::NI], bool live) {
-    if (!live) return;
-    static_assert(C::NI <= 32, "one bit per item");
-    typedef float fNI __attribute__((ext_vector_type(C::NI)));
+  // The largest margin score - T over the lane's items: vector ALU only (a
+  // chain of per-item ballots would stall on every scalar read of a compare
+  // result). T - T' < 0 for every non-NaN score below its T; a NaN score only
+  // matters to an ungated row, and then the margin is not used.
+  __device__ __forceinline__ float margin(const float (&sc)[C::NIH]) const {
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int j = 0; j < C::NIH; ++j) mx = fmaxf(mx, sc[j] - tq[j]);
+    return mx;
+  }
+
+  // The scores of sub-tile `sub` of a tile; k0: the sub-tile's first key.
+  __device__ __forceinline__ void take(int k0, int sub, const float (&sc)[C::NIH], float mx) {
+    static_assert(C::NIH <= 32, "one bit per item");
+    typedef float fNI __attribute__((ext_vector_type(C::NIH)));
     const int l = lane_id(), h = l >> 5, r32 = l & 31;
-    // raise each row's bin to the smallest bin its splits have published
-    if (pub && (steps - 1) % kShareEvery == 0) {
-      int g = 255;
-      for (int j = 0; j < S; ++j) g = min(g, (int)((gw >> (8 * j)) & 0xFFu));
-      g -= 1;
-      const bool raise = l < C::QW && row_on(qbase + l) && g > tau_v;
-      if (__ballot(raise) != 0) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (raise) {
-          const int lq = lane_here();
-          uint32_t ab = above[lq];
-          for (int t = tau_v + 1; t <= g; ++t) ab -= hist[lq * m + t];
-          move_tau(lq, g, ab);
+    if (sub == 0) {
+      // raise each row's bin to the smallest bin its splits have published
+      if (pub && (steps - 1) % kShareEvery == 0) {
+        int g = 255;
+        for (int j = 0; j < S; ++j) g = min(g, (int)((gw >> (8 * j)) & 0xFFu));
+        g -= 1;
+        const bool raise = l < C::QW && row_on(qbase + l) && g > tau_v;
+        if (__ballot(raise) != 0) {
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          if (raise) {
+            const int lq = lane_here();
+            uint32_t ab = above[lq];
+            for (int t = tau_v + 1; t <= g; ++t) ab -= hist[lq * m + t];
+            move_tau(lq, g, ab);
+          }
+          update_gates();
         }
-        update_gates();
+      }
+      // the periodic drain, at the same tile in every wave
+      if (use_queue && ++ntile % kDrainEvery == 0 && qlen != 0) {
+        drain();
+        refresh();
       }
     }
-    // the periodic drain, at the same tile in every wave
-    if (use_queue && ++ntile % kDrainEvery == 0 && qlen != 0) {
-      drain();
-      refresh();
-    }
-    // fast path, vector ALU only (a chain of per-item ballots would stall on
-    // every scalar read of a compare result): the largest margin score - T
-    // over the lane's items; T - T' < 0 for every non-NaN score below its T.
-    // A NaN score only matters to an ungated row, and then the fast path is
-    // skipped.
-    static_assert(C::NI == 2 * C::NIH, "items j and j + NIH share their query");
+    // (a gate raised just now may be above the margin's: the drain tests each
+    // score against its row's current gate)
     if (!ungated) {
-      float mx = -__builtin_inff();
-#pragma unroll
-      for (int j = 0; j < C::NIH; ++j) mx = fmaxf(mx, fmaxf(sc[j], sc[j + C::NIH]) - tq[j]);
       const bool lp = mx >= 0.0f;  // some score of this lane passes
       const uint64_t lm = __ballot(lp);
       if (lm == 0) return;  // wave-uniform: nothing passes
@@ -1158,12 +1197,12 @@ struct GroupedSink {
           drain();
           refresh();
         }
-        if (nrec <= kRecs) {
+        if (nrec <= kAppend) {
           if (lp) {
             const int slot = qlen + (int)mbcnt64(lm);
-            float* rp = rec + slot * C::NI;
+            float* rp = rec + slot * C::NIH;
 #pragma unroll
-            for (int v = 0; v < C::NI / 4; ++v)
+            for (int v = 0; v < C::NIH / 4; ++v)
               lds_put4(rp + 4 * v, f32x4_t{sc[4 * v], sc[4 * v + 1], sc[4 * v + 2], sc[4 * v + 3]});
             lds_put1(rhdr + slot, (uint32_t)(k0 - kq0) << 8 | (uint32_t)l);
           }
@@ -1176,21 +1215,20 @@ struct GroupedSink {
     // (built from the top item down: a compare and a shift-add of its result)
     uint32_t bits = 0;
 #pragma unroll
-    for (int it = C::NI - 1; it >= 0; --it) bits = shift_in_nlt(bits, sc[it], tq[it % C::NIH]);
+    for (int it = C::NIH - 1; it >= 0; --it) bits = shift_in_nlt(bits, sc[it], tq[it]);
     const uint32_t items = wave_or(bits);
     if (items == 0) return;
     fNI scv;
 #pragma unroll
-    for (int it = 0; it < C::NI; ++it) scv[it] = sc[it];
+    for (int it = 0; it < C::NIH; ++it) scv[it] = sc[it];
     // in place, one item at a time: every passing lane takes its slot and
     // counts at once
-    const bool inside = k0 >= vis_s && k0 + C::KT <= vis_e;
+    const bool inside = k0 >= vis_s && k0 + 32 <= vis_e;
+    const int key = k0 + r32;
     for (uint32_t rem = items; rem; rem &= rem - 1) {
       const int it = __builtin_ctz(rem);
       if (!((bits >> it) & 1u)) continue;
-      const int j = it % C::NIH, nt = it / C::NIH;
-      const int q = item_query(j, h);
-      const int key = k0 + nt * 32 + r32;
+      const int q = item_query(it, h);
       if (!inside) {
         const QState& r = qs[q];
         if (key < r.s || key >= r.e) continue;
@@ -1222,24 +1260,22 @@ struct GroupedSink {
     static_assert(kRecs <= kWave, "one record per lane");
     const int l = lane_here();
     if (l < qlen) {
-      const float* rp = rec + l * C::NI;
-      f32x4_t sv[C::NI / 4];
-      lds_get_n<C::NI / 4>(rp, sv);
+      const float* rp = rec + l * C::NIH;
+      f32x4_t sv[C::NIH / 4];
+      lds_get_n<C::NIH / 4>(rp, sv);
       const uint32_t hd = lds_get1(rhdr + l);
-      const int src = (int)(hd & 0xFFu), hs = src >> 5, k0 = kq0 + (int)(hd >> 8);
-      const int key0 = k0 + (src & 31);
+      const int src = (int)(hd & 0xFFu), hs = src >> 5;
+      const int key = kq0 + (int)(hd >> 8) + (src & 31);
       // the record's queries in its lane half: item_q(j, 0) + hs * 4 / H
       const QState* qh = qs + hs * (4 / C::H);
       uint32_t bits = 0;
 #pragma unroll
-      for (int it = C::NI - 1; it >= 0; --it)
-        bits = shift_in_nlt(bits, sv[it / 4][it % 4], qh[C::item_q(it % C::NIH, 0)].gate);
+      for (int it = C::NIH - 1; it >= 0; --it)
+        bits = shift_in_nlt(bits, sv[it / 4][it % 4], qh[C::item_q(it, 0)].gate);
       while (bits) {
         const int it = __builtin_ctz(bits);
         bits &= bits - 1;
-        const int j = it % C::NIH, nt = it / C::NIH;
-        const int q = item_query(j, hs);
-        const int key = key0 + nt * 32;
+        const int q = item_query(it, hs);
         const float s = __uint_as_float(lds_get1(reinterpret_cast<const uint32_t*>(rp) + it));
         f32x4_t f;
         i32x4_t g;

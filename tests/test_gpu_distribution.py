@@ -110,6 +110,8 @@ def test_fused_sorted_rows(lib, nq, splits, k):
     (128, 8191, 64, 128, "bf16", "dsa", 64, dict(force_fallback=True)),
     (129, 8191, 64, 128, "bf16", "dsa", 64, dict(force_fallback=True)),
     (40, 20000, 1, 128, "bf16", "ip", 200, dict(key_splits=4, capacity=400)),
+    (300, 4001, 1, 128, "bf16", "dsa", 2000, dict()),  # most lanes pass in most sub-tiles
+    (33, 4001, 4, 64, "f32", "dsa", 1000, dict(sample_size=0)),  # no gate at first
 ])
 def test_fused_few_tiles(lib, nq, nk, h, d, dtype, mode, k, opt):
     x = workloads.exact_inputs(nq, nk, h, d, dtype, seed=nq + nk)
