@@ -155,8 +155,9 @@ __global__ __launch_bounds__(kFreqThreads) void k_freq_count(const int32_t* prev
 }
 
 // One wave picks the digit of `pass` from its histogram h: lane l owns digits
-// [l * per, (l + 1) * per), read once into registers.
-__device__ void freq_pick(int pass, const uint32_t* h, FreqState* fs) {
+// [l * per, (l + 1) * per), read once into registers. in: the state before
+// the pass; one lane writes the state after it to out.
+__device__ void freq_pick(int pass, const uint32_t* h, const FreqState& in, FreqState* out) {
   constexpr int kPer = kFreqBins / kWave;
   const int l = lane_id();
   const int nb = pass == kFreqClampPass ? kFreqBins : 1 << freq_bits(pass), per = nb / kWave;
@@ -166,7 +167,7 @@ __device__ void freq_pick(int pass, const uint32_t* h, FreqState* fs) {
   uint32_t loc = 0;
 #pragma unroll
   for (int j = 0; j < kPer; ++j) loc += hr[j];
-  const uint32_t want = fs->want;
+  const uint32_t want = in.want;
   uint32_t run = wave_suffix_sum_excl(loc);  // matching keys with a digit above this lane's range
   int dig = -1;
   uint32_t gt = 0;
@@ -193,7 +194,7 @@ __device__ void freq_pick(int pass, const uint32_t* h, FreqState* fs) {
   }
   const bool writer = found ? dig >= 0 : l == 0;
   if (writer) {
-    FreqState s = *fs;
+    FreqState s = in;
     if (pass == kFreqClampPass) {
       s.prefix = (uint32_t)dig;
       s.mask = ~0u;
@@ -205,7 +206,7 @@ __device__ void freq_pick(int pass, const uint32_t* h, FreqState* fs) {
     }
     s.above += gt;
     s.want = want - gt;
-    *fs = s;
+    *out = s;
   }
 }
 
@@ -223,9 +224,10 @@ __device__ __forceinline__ void freq_hist_add(uint32_t* h, bool match, uint32_t 
 
 // One wave picks the digit of a pass, in a launch of its own: a release fence
 // in every histogram block (so that the last one could pick) writes back the
-// L2s and cost more than the launch.
+// L2s and cost more than the launch. (The clamped pass, whose state before it
+// is known, needs no launch: k_freq_blocks.)
 __global__ __launch_bounds__(kWave) void k_freq_pick(int pass, const uint32_t* hist, FreqState* fs) {
-  freq_pick(pass, hist + pass * kFreqBins, fs);
+  freq_pick(pass, hist + pass * kFreqBins, *fs, fs);
 }
 
 __global__ __launch_bounds__(kFreqThreads) void k_freq_hist(const uint32_t* counts, int nk, int pass,
@@ -259,6 +261,7 @@ __global__ __launch_bounds__(kFreqThreads) void k_freq_hist(const uint32_t* coun
 // histograms and the selection state.
 constexpr int kFreqRange = 16384;
 constexpr int kFreqParts = 32;
+constexpr int kFreqPart = 8192;  // entries: a step of every thread's loads
 constexpr int kFreqLdsMaxKeys = 262144;
 
 __global__ __launch_bounds__(kFreqThreads) void k_freq_count_lds(const int32_t* prev, int64_t ld, int rows, int pk,
@@ -324,13 +327,16 @@ __global__ __launch_bounds__(kFreqThreads) void k_freq_merge(const uint32_t* par
   for (int64_t s = (int64_t)blockIdx.x * kFreqThreads + threadIdx.x; s < span; s += stride) {
     uint32_t c = 0;
     if (s < nk) {
-      uint32_t c4[4] = {0u, 0u, 0u, 0u};
+      constexpr int kU = 16;  // chunk counts read at once
       int ch = 0;
-      for (; ch + 4 <= nparts; ch += 4)
+      for (; ch + kU <= nparts; ch += kU) {
+        uint32_t cu[kU];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c4[u] += part[(int64_t)(ch + u) * nk + s];
-      for (; ch < nparts; ++ch) c4[0] += part[(int64_t)ch * nk + s];
-      c = c4[0] + c4[1] + c4[2] + c4[3];
+        for (int u = 0; u < kU; ++u) cu[u] = part[(int64_t)(ch + u) * nk + s];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) c += cu[u];
+      }
+      for (; ch < nparts; ++ch) c += part[(int64_t)ch * nk + s];
       counts[s] = c;
     }
     if (clamp) freq_hist_add(h, s < nk, min(c, (uint32_t)(kFreqBins - 1)), l);
@@ -354,10 +360,22 @@ __device__ __forceinline__ FreqSel freq_sel(const FreqState* fs) {
   return FreqSel{s.prefix, s.prefix > 0u ? s.want : 0u};
 }
 
-__global__ __launch_bounds__(kFreqThreads) void k_freq_blocks(const uint32_t* counts, int nk, int chunk,
-                                                               const FreqState* fs, uint32_t* bc) {
+// Per block of `chunk` keys, its keys with count > c* and = c*. With `clamp`
+// every block first picks c* from the clamped pass's histogram (8 KB from the
+// L2, in place of a launch of its own) and block 0 stores the state for
+// k_freq_emit.
+__global__ __launch_bounds__(kFreqThreads) void k_freq_blocks(const uint32_t* counts, int nk, int chunk, bool clamp,
+                                                               int ns, const uint32_t* hist, FreqState* fs,
+                                                               uint32_t* bc) {
   __shared__ uint32_t tmp[kFreqThreads / kWave];
-  const FreqSel f = freq_sel(fs);
+  __shared__ FreqState picked;
+  if (clamp) {
+    if (threadIdx.x < kWave)
+      freq_pick(kFreqClampPass, hist + kFreqClampPass * kFreqBins, FreqState{0u, 0u, (uint32_t)ns, 0u}, &picked);
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) *fs = picked;
+  }
+  const FreqSel f = freq_sel(clamp ? &picked : fs);
   const int64_t lo = (int64_t)blockIdx.x * chunk, hi = std::min<int64_t>(lo + chunk, nk);
   uint32_t g = 0, e = 0;
   for (int64_t s = lo + threadIdx.x; s < hi; s += kFreqThreads) {
@@ -439,30 +457,31 @@ hipError_t launch_sample_from_topk(const int32_t* prev, int64_t ld, int rows, in
   // fewer than ns keys can reach a count of kFreqBins - 1: one clamped pass
   const bool clamp = entries / (kFreqBins - 1) < ns;
   if (nk > 0 && nk <= kFreqLdsMaxKeys) {
-    // about 128 counting blocks; the merge reads each key's chunk counts
-    // with one thread per key
+    // a counting block per CU (their loads' latency bounds them), of kFreqPart
+    // entries at least; the merge reads each key's chunk counts with one
+    // thread per key. 1024 lists of 2048 keys, 131072 keys: 41.2 us a call with
+    // 128 blocks, four loads of the merge in flight and a launch for the pick,
+    // 33.8 so.
     const int ranges = (nk + kFreqRange - 1) / kFreqRange;
-    const int nparts = std::max(1, std::min(kFreqParts, 128 / ranges));
+    const int nparts = (int)std::max<int64_t>(
+        1, std::min<int64_t>({kFreqParts, 256 / ranges, (entries + kFreqPart - 1) / kFreqPart}));
     const int mgrid = (nk + kFreqThreads - 1) / kFreqThreads;
     hipLaunchKernelGGL(k_freq_count_lds, dim3(ranges, nparts), dim3(kFreqThreads), 0, st, prev, ld, rows, pk, nk,
                        part, hist, fs, ns);
     hipLaunchKernelGGL(k_freq_merge, dim3(mgrid), dim3(kFreqThreads), 0, st, part, nparts, nk, clamp, counts, hist);
-    if (clamp) hipLaunchKernelGGL(k_freq_pick, dim3(1), dim3(kWave), 0, st, kFreqClampPass, hist, fs);
   } else {
     hipLaunchKernelGGL(k_freq_zero, dim3(sweep), dim3(kFreqThreads), 0, st, counts, nk, hist, fs, ns);
     if (entries > 0)
       hipLaunchKernelGGL(k_freq_count, dim3(cgrid), dim3(kFreqThreads), 0, st, prev, ld, rows, pk, nk, counts);
-    if (clamp) {
+    if (clamp)
       hipLaunchKernelGGL(k_freq_hist, dim3(sweep), dim3(kFreqThreads), 0, st, counts, nk, kFreqClampPass, fs, hist);
-      hipLaunchKernelGGL(k_freq_pick, dim3(1), dim3(kWave), 0, st, kFreqClampPass, hist, fs);
-    }
   }
   if (!clamp)
     for (int pass = 0; pass < 3; ++pass) {
       hipLaunchKernelGGL(k_freq_hist, dim3(sweep), dim3(kFreqThreads), 0, st, counts, nk, pass, fs, hist);
       hipLaunchKernelGGL(k_freq_pick, dim3(1), dim3(kWave), 0, st, pass, hist, fs);
     }
-  hipLaunchKernelGGL(k_freq_blocks, dim3(nb), dim3(kFreqThreads), 0, st, counts, nk, chunk, fs, bc);
+  hipLaunchKernelGGL(k_freq_blocks, dim3(nb), dim3(kFreqThreads), 0, st, counts, nk, chunk, clamp, ns, hist, fs, bc);
   hipLaunchKernelGGL(k_freq_emit, dim3(nb), dim3(kFreqThreads), 0, st, counts, nk, chunk, fs, bc, ns, out);
   return hipGetLastError();
 }

@@ -99,6 +99,16 @@ def test_sample_from_topk_around_the_lds_count_limit(lib, nk):
         np.testing.assert_array_equal(_gpu_sample(prev, nk, ns), orc.sample_from_topk(prev, nk, ns))
 
 
+@pytest.mark.parametrize("rows,k,nk", [(1, 8191, 16384), (1, 8193, 16384), (2, 8192, 16385), (17, 8191, 16383),
+                                       (33, 8192, 16384), (40, 8192, 100003), (3, 4001, 262144)])
+def test_sample_from_topk_entry_chunks(lib, rows, k, nk):
+    """Entry counts around one counting chunk (8192), and 1 to 32 chunks a key
+    range, with whole and broken merge steps of 16 chunks."""
+    rng = np.random.default_rng(rows * 7 + k)
+    prev = (nk * rng.random((rows, k)) ** 2).astype(np.int32)
+    np.testing.assert_array_equal(_gpu_sample(prev, nk, 3000), orc.sample_from_topk(prev, nk, 3000))
+
+
 def test_sample_from_topk_strided_rows_and_limits(lib):
     """prev_idx with a row stride larger than k (a column slice), nk < ns, and
     the longest list."""
