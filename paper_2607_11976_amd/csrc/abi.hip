@@ -42,6 +42,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct Resolved {
   int k, m, ns, cap, S, L, E;
   int HS;                  // histograms per row: S, or 1 when shared by the splits
+  int S0, cap0;            // the lists the workspace is sized for (S of cap fit in their bytes)
   bool shared;             // the wide scan: one histogram and threshold per row
   uint32_t flags;
   uint64_t seed;
@@ -93,9 +94,15 @@ Layout carve(int nq, int nk, const Resolved& r, bool fused) {
   L.params = take((size_t)nq * sizeof(RowParam));
   L.list = take((size_t)r.ns * 4);
   L.samp = fused ? take((size_t)nq * r.ns * 4) : 0;
+  const size_t lists = off;
   L.cnt = take((size_t)nq * r.S * 4);
   L.hist = take((size_t)nq * r.HS * r.m * 4);
   L.cand = take((size_t)nq * r.S * r.cap * 8);
+  // the size of the call does not depend on how resolve_fused splits the
+  // bytes of the S0 lists (that choice looks at visible_start)
+  off = std::max(off, lists + align256((size_t)nq * r.S0 * 4) +
+                          align256((size_t)nq * (r.shared ? 1 : r.S0) * r.m * 4) +
+                          align256((size_t)nq * r.S0 * r.cap0 * 8));
   L.gate = fused ? take((size_t)nq * 8) : 0;  // published bins: [nq] ints (wide), [nq][8] bytes
   const FallbackShape fs = fallback_shape(nq, nk);
   L.scratch = fused ? take((size_t)fs.grid * fs.batch * nk * 4) : 0;
@@ -194,14 +201,16 @@ Resolved resolve_fused(const lt_options* o, int nq, int nk, int k, int mode, con
       if (blocks * 10 >= rounds * kTargetBlocks * 9) break;
     }
   }
+  r.S0 = S;
+  r.cap0 = r.cap;
   auto split_len = [&](int s) {
     const int per = (nk + s - 1) / s;
     return std::max(1, (per + sh.keys_per_step - 1) / sh.keys_per_step) * sh.keys_per_step;
   };
   if (o->key_splits == 0 && o->capacity <= 0 && !r.shared && (r.starts || 3 * tiles * S <= 2 * kTargetBlocks)) {
-    // More splits, within the memory that these take (so a workspace sized
-    // without visible_start serves, and no shape outgrows the static one),
-    // their lists that much shorter:
+    // More splits, within the memory that these take (carve reserves it: a
+    // workspace sized without visible_start serves with it, and no shape
+    // outgrows the static one), their lists that much shorter:
     // * packed sequences: the tiles see ranges of different lengths, so blocks
     //   of equal splits end at different times; kPackedRounds blocks per CU
     //   even that out (1251 queries of four sequences of 3 to 41 K keys, bf16:
@@ -256,6 +265,8 @@ Resolved resolve_scores(const lt_options* o, int nq, int nk, int k) {
   const int per = (nk + r.S - 1) / r.S;
   r.L = std::max(256, ((per + 255) / 256) * 256);
   r.cap = std::min(r.cap, r.L);  // a split never holds more candidates than keys
+  r.S0 = r.S;
+  r.cap0 = r.cap;
   return r;
 }
 

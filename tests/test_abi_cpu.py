@@ -87,6 +87,33 @@ def test_workspace_sizes(lib):
     assert lt.lt_sample_from_topk_workspace_size(-1) == 0
 
 
+# few and many query tiles, splits of one tile and of many, lists that hold a
+# whole split and lists that do not
+@pytest.mark.parametrize("h,d,dtype,mode", [
+    (64, 128, lt.LT_BF16, lt.LT_SCORE_DSA), (64, 128, lt.LT_FP8_E4M3FN, lt.LT_SCORE_DSA),
+    (4, 64, lt.LT_F32, lt.LT_SCORE_DSA), (4, 128, lt.LT_BF16, lt.LT_SCORE_DSA), (1, 128, lt.LT_BF16, lt.LT_SCORE_IP),
+    (1, 64, lt.LT_F32, lt.LT_SCORE_IP), (1, 768, lt.LT_BF16, lt.LT_SCORE_IP)])
+def test_fused_workspace_size_ignores_visible_start(lib, h, d, dtype, mode):
+    packed = lt.lt_options_default()
+    packed.visible_start = 256
+    for nq in (1, 2, 8, 33, 100, 1251, 4096):
+        for nk in (64, 1000, 4096, 20000, 73016, 100003, 400000):
+            for k in (16, 64, 512, 2048, 8192):
+                plain = lt.lt_indexer_topk_workspace_size(nq, nk, h, d, dtype, mode, k)
+                assert lt.lt_indexer_topk_workspace_size(nq, nk, h, d, dtype, mode, k, packed) == plain, (nq, nk, k)
+
+
+def test_fused_workspace_size_does_not_fall_as_keys_grow(lib):
+    # a decode loop: the workspace of the longest context serves every shorter
+    # one, also where each split is one key tile (key counts around multiples
+    # of 64 and 256 keys a split)
+    for h, d, dtype, top in ((64, 128, lt.LT_BF16, 9000), (4, 64, lt.LT_F32, 4500), (1, 128, lt.LT_BF16, 4500)):
+        for k in (64, 2048):
+            sizes = [lt.lt_indexer_topk_workspace_size(2, nk, h, d, dtype, lt.LT_SCORE_DSA, k)
+                     for nk in range(k, top, 37)]
+            assert sizes == sorted(sizes), (h, k)
+
+
 def test_argument_checks_reject_before_any_device_work(lib):
     P = 256  # a fake, aligned, never dereferenced address
     # null q
