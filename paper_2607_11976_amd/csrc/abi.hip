@@ -42,7 +42,9 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct Resolved {
   int k, m, ns, cap, S, L, E;
   int HS;                  // histograms per row: S, or 1 when shared by the splits
-  int S0, cap0;            // the lists the workspace is sized for (S of cap fit in their bytes)
+  // the lists, histograms and list entries (of all rows) that the workspace is
+  // sized for; what the call uses of them fits in their bytes
+  int64_t lists0, hists0, entries0;
   bool shared;             // the wide scan: one histogram and threshold per row
   uint32_t flags;
   uint64_t seed;
@@ -98,11 +100,8 @@ Layout carve(int nq, int nk, const Resolved& r, bool fused) {
   L.cnt = take((size_t)nq * r.S * 4);
   L.hist = take((size_t)nq * r.HS * r.m * 4);
   L.cand = take((size_t)nq * r.S * r.cap * 8);
-  // the size of the call does not depend on how resolve_fused splits the
-  // bytes of the S0 lists (that choice looks at visible_start)
-  off = std::max(off, lists + align256((size_t)nq * r.S0 * 4) +
-                          align256((size_t)nq * (r.shared ? 1 : r.S0) * r.m * 4) +
-                          align256((size_t)nq * r.S0 * r.cap0 * 8));
+  off = std::max(off, lists + align256((size_t)r.lists0 * 4) + align256((size_t)r.hists0 * r.m * 4) +
+                          align256((size_t)r.entries0 * 8));
   L.gate = fused ? take((size_t)nq * 8) : 0;  // published bins: [nq] ints (wide), [nq][8] bytes
   const FallbackShape fs = fallback_shape(nq, nk);
   L.scratch = fused ? take((size_t)fs.grid * fs.batch * nk * 4) : 0;
@@ -201,8 +200,10 @@ Resolved resolve_fused(const lt_options* o, int nq, int nk, int k, int mode, con
       if (blocks * 10 >= rounds * kTargetBlocks * 9) break;
     }
   }
-  r.S0 = S;
-  r.cap0 = r.cap;
+  // (also where the splits below differ: they look at visible_start)
+  r.lists0 = (int64_t)nq * S;
+  r.hists0 = r.shared ? nq : r.lists0;
+  r.entries0 = r.lists0 * r.cap;
   auto split_len = [&](int s) {
     const int per = (nk + s - 1) / s;
     return std::max(1, (per + sh.keys_per_step - 1) / sh.keys_per_step) * sh.keys_per_step;
@@ -243,30 +244,47 @@ Resolved resolve_fused(const lt_options* o, int nq, int nk, int k, int mode, con
   return r;
 }
 
-Resolved resolve_scores(const lt_options* o, int nq, int nk, int k) {
+// split: rows may be split where key_splits is 0 (see lt_topk_select).
+Resolved resolve_scores(const lt_options* o, int nq, int nk, int k, bool split) {
   Resolved r{};
   resolve_common(o, k, r);
   lt_options d;
   lt_options_default(&d);
   if (!o) o = &d;
   r.ns = resolve_sample(o, r, nk, k, LT_SCORE_DSA, false);
+  const int64_t cap = r.cap;
   int S = 1;
+  r.lists0 = nq;
+  r.entries0 = nq * cap;
   if (o->key_splits > 0) {
     S = o->key_splits;
-  } else if (nq > 0 && nq < kTargetBlocks) {
+  } else if (split && nq > 0 && nq < kTargetBlocks) {
     // few rows: splits up to a block per CU. Each refreshes its own
     // threshold and keeps about k (1 + ln(keys / 3k)) candidates, so short
     // splits cost the select more than they save here: at least
-    // kMinScoresSplitKeys keys and kMinScoresSplitK * k
-    S = std::min({(kTargetBlocks + nq - 1) / nq, nk / kMinScoresSplitKeys, nk / kMinScoresSplitK / k});
+    // kMinScoresSplitKeys keys and kMinScoresSplitK * k. (One split more, past
+    // a block per CU: 100 rows of 262144 keys, k = 2048, 78 -> 104 us a call;
+    // 200 of 131072, 77 -> 88; 200 of 262144, k = 64, 277 -> 250.)
+    S = std::min({kTargetBlocks / nq, nk / kMinScoresSplitKeys, nk / kMinScoresSplitK / k});
+    // the workspace holds the most lists that any choice of fewer rows, keys
+    // or a smaller k makes, so that a program's largest call sizes it for the
+    // others too; it stays within what kTargetBlocks unsplit rows take
+    r.lists0 = std::max<int64_t>(nq, std::min<int64_t>(kTargetBlocks, (int64_t)nq * (nk / kMinScoresSplitKeys)));
+    r.entries0 = r.lists0 * cap;
+    // (S lists of 12k entries, S at most nk / kMinScoresSplitK / k)
+    if (o->capacity <= 0)
+      r.entries0 = std::min(r.entries0, nq * std::max(cap, (int64_t)nk * 12 / kMinScoresSplitK));
   }
   r.S = std::max(1, std::min(S, (nk + 255) / 256 + 1));
   r.HS = r.S;
   const int per = (nk + r.S - 1) / r.S;
   r.L = std::max(256, ((per + 255) / 256) * 256);
+  if (o->key_splits > 0) {
+    r.lists0 = (int64_t)nq * r.S;
+    r.entries0 = r.lists0 * cap;
+  }
+  r.hists0 = r.lists0;
   r.cap = std::min(r.cap, r.L);  // a split never holds more candidates than keys
-  r.S0 = r.S;
-  r.cap0 = r.cap;
   return r;
 }
 
@@ -477,7 +495,7 @@ int lt_indexer_scores(const void* q, const float* q_scale, const float* w, const
 
 size_t lt_topk_select_workspace_size(int32_t nq, int32_t nk, int32_t k, const lt_options* opts) {
   if (nq < 0 || nk < 0 || k < 1 || k > LT_K_MAX) return 0;
-  Resolved r = resolve_scores(opts, nq, nk, k);
+  Resolved r = resolve_scores(opts, nq, nk, k, true);
   if (r.status) return 0;
   return carve(nq, nk, r, false).total;
 }
@@ -497,10 +515,15 @@ int lt_topk_select(const float* scores, int64_t stride, int32_t nq, int32_t nk, 
   if (rc) return rc;
   if (nq == 0) return LT_OK;
   if (!out_idx || !out_scores || !workspace || !aligned(workspace, 256)) return LT_EINVAL;
-  const Resolved r = resolve_scores(opts, nq, nk, k);
+  Resolved r = resolve_scores(opts, nq, nk, k, true);
   if (r.status) return r.status;
-  const Layout L = carve(nq, nk, r, false);
-  if (workspace_bytes < L.total) return LT_EWORKSPACE;
+  Layout L = carve(nq, nk, r, false);
+  if (workspace_bytes < L.total) {
+    // one list per row in a workspace that has no room for the splits' lists
+    r = resolve_scores(opts, nq, nk, k, false);
+    L = carve(nq, nk, r, false);
+    if (workspace_bytes < L.total) return LT_EWORKSPACE;
+  }
   hipStream_t st = (hipStream_t)stream;
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   uint32_t* qctl = reinterpret_cast<uint32_t*>(ws + L.qctl);

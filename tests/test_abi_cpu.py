@@ -114,6 +114,27 @@ def test_fused_workspace_size_does_not_fall_as_keys_grow(lib):
             assert sizes == sorted(sizes), (h, k)
 
 
+def _rising(values):
+    return sorted(set(values))
+
+
+def test_select_workspace_size_does_not_fall_as_rows_keys_or_k_grow(lib):
+    # a program sizes the workspace for its largest call and reuses it
+    rows = _rising([1, 2, 3, 7, 16, 64, 85, 86, 100, 127, 128, 129, 200, 255, 256, 257, 1000])
+    keys = _rising([1, 255, 4096, 16383, 16384, 32767, 32768, 50000, 65536, 131072, 262144, 1000003, 5000000])
+    ks = _rising([1, 16, 64, 170, 171, 300, 511, 512, 1000, 1024, 1100, 2048, 4096, 8192])
+    capped = lt.lt_options_default()
+    capped.capacity = 3000
+    for o in (None, capped):
+        size = {(q, n, k): lt.lt_topk_select_workspace_size(q, n, k, o) for q in rows for n in keys for k in ks}
+        for axis, vals in enumerate((rows, keys, ks)):
+            for at, s in size.items():
+                nxt = vals.index(at[axis]) + 1
+                if nxt < len(vals):
+                    up = at[:axis] + (vals[nxt],) + at[axis + 1:]
+                    assert s <= size[up], (at, up)
+
+
 def test_argument_checks_reject_before_any_device_work(lib):
     P = 256  # a fake, aligned, never dereferenced address
     # null q

@@ -67,6 +67,22 @@ def test_scores_in_filter_shapes(lib, nq, nk, k, kind, sorted_out):
     _check(scores, nk, k, offs, starts, gi, gs, sorted_out, sorted({0, 1 % nq, nq // 2, nq - 1}))
 
 
+# a workspace with no room for the lists of split rows (here: of the call with
+# one split, which is what fewer than 256 rows took before they were split)
+@pytest.mark.parametrize("nq,nk,k", [(1, 140001, 100), (60, 66000, 300), (200, 33000, 64)])
+def test_scores_in_workspace_for_unsplit_rows(lib, nq, nk, k):
+    scores = _rows("normal", nq, nk, seed=nq)
+    n = lt.lt_topk_select_workspace_size(nq, nk, k, lt.make_options(key_splits=1))
+    assert n <= lt.lt_topk_select_workspace_size(nq, nk, k)
+    ws = torch.empty(n + 4096, dtype=torch.uint8, device="cuda")
+    ws[n:] = 123
+    gi, gs = lt.topk_select(scores.cuda(), k, nk, None, options=lt.make_options(sorted_output=True), workspace=ws[:n])
+    assert bool((ws[n:] == 123).all())
+    _check(scores, nk, k, None, None, gi.cpu().numpy(), gs.cpu().numpy(), True, sorted({0, nq // 2, nq - 1}))
+    with pytest.raises(lt.LiteTopKError):
+        lt.topk_select(scores.cuda(), k, nk, None, workspace=ws[:n - 256])
+
+
 # 256-thread blocks for many short rows, else 1024; k = 2048 and 2049 are the
 # last with 4096 sort entries and the first with more
 @pytest.mark.parametrize("nq,nk,k", [(600, 3000, 100), (600, 16385, 2048), (40, 16384, 2049), (5, 70001, 8192),
