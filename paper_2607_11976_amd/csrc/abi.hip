@@ -1,5 +1,6 @@
 // C ABI of the library (include/litetopk.h): argument checks, option
 // resolution, workspace carving and the stream-ordered launch sequence.
+#include <limits.h>
 #include <string.h>
 
 #include <algorithm>
@@ -275,10 +276,10 @@ Resolved resolve_scores(const lt_options* o, int nq, int nk, int k, bool split) 
     if (o->capacity <= 0)
       r.entries0 = std::min(r.entries0, nq * std::max(cap, (int64_t)nk * 12 / kMinScoresSplitK));
   }
-  r.S = std::max(1, std::min(S, (nk + 255) / 256 + 1));
+  r.S = std::max(1, std::min(S, nk / 256 + 2 - (nk % 256 == 0)));
   r.HS = r.S;
-  const int per = (nk + r.S - 1) / r.S;
-  r.L = std::max(256, ((per + 255) / 256) * 256);
+  const int64_t per = ((int64_t)nk + r.S - 1) / r.S;
+  r.L = (int)std::max<int64_t>(256, std::min<int64_t>((per + 255) / 256 * 256, INT_MAX));
   if (o->key_splits > 0) {
     r.lists0 = (int64_t)nq * r.S;
     r.entries0 = r.lists0 * cap;

@@ -289,9 +289,11 @@ __global__ __launch_bounds__(NTH) void k_filter(const float* scores, int64_t str
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), l = lane_id();
   const int unit = blockIdx.x, row = unit / S, split = unit - row * S;
   const RowRange rr = row_range(offs, starts, row, nk);
-  // the split's share of the row's range (at most L keys)
-  const int part = min(L, ((rr.e - rr.s + S - 1) / S + 255) & ~255);
-  const int lo = rr.s + min(split * part, rr.e - rr.s), hi = min(lo + part, rr.e);
+  // the split's share of the row's range (at most L keys; positions unsigned,
+  // here and below: a row may have up to 2^31 - 1 keys)
+  const uint32_t range = rr.e - rr.s;
+  const uint32_t part = min((uint32_t)L, ((range + S - 1) / S + 255) & ~255u);
+  const int lo = rr.s + (int)min(split * part, range), hi = lo + (int)min(part, (uint32_t)(rr.e - lo));
   const RowParam p = params[row];
   float thr = gate_thr(p.tau0);
   for (int b = threadIdx.x; b < kMaxBins; b += NTH) hist[b] = 0u;
@@ -300,18 +302,18 @@ __global__ __launch_bounds__(NTH) void k_filter(const float* scores, int64_t str
   int2* out = cand + (int64_t)unit * cap;
   uint32_t tail = 0, fresh = 0;
   const uint32_t refresh_at = max((uint32_t)k / kRefreshShare, 8u);
-  const int len = hi - lo;
+  const uint32_t len = hi - lo;
   // a descriptor per step whose range check turns the keys past hi into
   // zeros without a branch (they are masked below)
   const uint64_t base = (uint64_t)(scores + (int64_t)row * stride + lo);
   const float* ubase = (const float*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)base) |
                                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32);
-  const int ulen = __builtin_amdgcn_readfirstlane(len);
-  const int woff = wave * kWave * U;  // the wave's keys of a step: [step + woff, + kWave * U)
-  auto load = [&](int off, float (&v)[U]) {
-    const int left = ulen - off - woff;
+  const uint32_t ulen = __builtin_amdgcn_readfirstlane(len);
+  const uint32_t woff = wave * kWave * U;  // the wave's keys of a step: [step + woff, + kWave * U)
+  auto load = [&](uint32_t off, float (&v)[U]) {
+    const uint32_t at = off + woff;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(ubase + off + woff), 0, left > 0 ? (int)((uint32_t)min(left, kWave * U) * 4u) : 0, kBufferRaw);
+        (void*)(ubase + at), 0, at < ulen ? (int)(min(ulen - at, (uint32_t)(kWave * U)) * 4u) : 0, kBufferRaw);
 #pragma unroll
     for (int u = 0; u < U; ++u)
       v[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, l * 4 + u * kWave * 4, 0, 0));
@@ -330,8 +332,8 @@ __global__ __launch_bounds__(NTH) void k_filter(const float* scores, int64_t str
       total += t;
     }
   };
-  auto step = [&](int off, const float (&v)[U]) {
-    const int rel = off + woff + l;  // position of item 0 in the split
+  auto step = [&](uint32_t off, const float (&v)[U]) {
+    const uint32_t rel = off + woff + l;  // position of item 0 in the split
     uint32_t bits = 0, mine = 0;     // bit u: item u passes; the wave's passing keys
     auto gate = [&]() {
       bits = mine = 0;
@@ -366,7 +368,7 @@ __global__ __launch_bounds__(NTH) void k_filter(const float* scores, int64_t str
         const bool ps = (bits >> u) & 1u;
         const uint64_t mask = __ballot(ps);
         const uint32_t pos = at + mbcnt64(mask);
-        if (ps && pos < (uint32_t)cap) out[pos] = make_int2(lo + rel + u * kWave, __float_as_int(v[u]));
+        if (ps && pos < (uint32_t)cap) out[pos] = make_int2(lo + (int)(rel + u * kWave), __float_as_int(v[u]));
         at += (uint32_t)__popcll(mask);
       }
     }
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(NTH) void k_filter(const float* scores, int64_t str
   if (ulen > 0) {
     float va[U], vb[U];
     load(0, va);
-    for (int off = 0; off < ulen; off += 2 * STEP) {
+    for (uint32_t off = 0; off < ulen; off += 2 * STEP) {
       load(off + STEP, vb);
       step(off, va);
       load(off + 2 * STEP, va);
@@ -996,8 +998,8 @@ __global__ __launch_bounds__(kSelThreads) void k_fallback_scores(
     const int e = blockIdx.x / chunks, c = blockIdx.x - e * chunks;
     const int row = queue[e];
     const RowRange rr = row_range(offs, starts, row, nk);
-    const int len = rr.e > rr.s ? rr.e - rr.s : 0, per = (len + chunks - 1) / chunks;
-    const int kb = min(rr.s + c * per, rr.s + len), ke = min(kb + per, rr.s + len);
+    const int len = rr.e > rr.s ? rr.e - rr.s : 0, per = (int)(((uint32_t)len + chunks - 1) / chunks);
+    const int kb = rr.s + (int)min((int64_t)c * per, (int64_t)len), ke = kb + min(per, rr.s + len - kb);
     const int64_t cb = (int64_t)e * chunks * k;
     split_fallback_select<kSelThreads>(scores + (int64_t)row * stride, rr.s, len, per, chunks, c, kb, ke, k,
                                        cidx + cb, cscore + cb, &qctl[kQctlDone + e], out_i + (int64_t)row * k,
@@ -1084,7 +1086,8 @@ __device__ __forceinline__ bool radix_row(const float* rowp, int n, int k, int E
   const uint32_t slots = (uint32_t)sort_slots(E);
   uint32_t* bk = reinterpret_cast<uint32_t*>(e2 + slots);
   const int tid = threadIdx.x, l = lane_id(), wave = tid / kWave;
-  if (n <= k) return false;
+  // (the loads run up to two steps past the row's end, in 32-bit positions)
+  if (n <= k || n > INT_MAX - 2 * RadixRow<NTH>::STEP) return false;
   RadixRow<NTH> rr;
   rr.init(rowp, n);
   // ---- span of the order keys ----

@@ -302,7 +302,7 @@ __device__ __forceinline__ void split_fallback_select(const float* srow, int rs,
                                                       int kb, int ke, int k, int32_t* cidx, float* cscore,
                                                       uint32_t* counter, int32_t* oi, float* os, bool sorted,
                                                       uint8_t* lds, int* flag) {
-  auto clen = [&](int j) { return max(0, min(per, len - j * per)); };
+  auto clen = [&](int j) { return (int)max((int64_t)0, min((int64_t)per, len - (int64_t)j * per)); };
   int off = 0;
   for (int j = 0; j < c; ++j) off += min(k, clen(j));
   radix_select_row<NTH>(srow + kb, ke - kb, k, cidx + off, cscore + off, false, lds, kb, false);
@@ -353,7 +353,7 @@ constexpr int kRadixUnroll = LT_RADIX_UNROLL;
 // wait for every load in flight). s0 and s1 are wave-uniform,
 // s1 - s0 < 2^30.
 template <int U, class Body>
-__device__ __forceinline__ void wave_stream(const float* row, int s0, int s1, Body&& body) {
+__device__ __forceinline__ void wave_stream(const float* row, uint32_t s0, uint32_t s1, Body&& body) {
   constexpr int S = kWave * U;
   // the descriptor lives in scalar registers: the address and length are
   // made wave-uniform explicitly (a caller's arguments may sit in vector
@@ -440,9 +440,9 @@ __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k,
     return;
   }
   // this wave's segment [s0, s1) of the row
-  const int seg = ((n + NW - 1) / NW + kWave - 1) / kWave * kWave;
+  const uint32_t seg = (((uint32_t)n + NW - 1) / NW + kWave - 1) / kWave * kWave;
   const int wv = __builtin_amdgcn_readfirstlane(wave);
-  const int s0 = min(wv * seg, n), s1 = min(s0 + seg, n);
+  const uint32_t s0 = min(wv * seg, (uint32_t)n), s1 = min(s0 + seg, (uint32_t)n);
 
   uint32_t prefix = 0, pmask = 0, remaining = (uint32_t)k;
   uint32_t gbefore = 0;  // this wave's keys above the digits chosen so far (wave-uniform)
@@ -461,10 +461,10 @@ __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k,
       __syncthreads();
       uint32_t g = 0;
       for (int w = 0; w < wv; ++w) g += tmp[w];
-      wave_stream<U>(row, s0, s1, [&](int c0, const float (&x)[U]) {
+      wave_stream<U>(row, s0, s1, [&](uint32_t c0, const float (&x)[U]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int i = c0 + u * kWave + l;
+          const uint32_t i = c0 + u * kWave + l;
           const bool v = i < s1;
           const uint32_t kp = ord_key(x[u]) & pmask;
           const bool ab = v & (kp > prefix), in = v & (kp == prefix);
@@ -507,7 +507,7 @@ __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k,
     // bytes, so the lanes of the few most common bins add their counts with
     // one atomic per bin
     auto hist_pass = [&]<bool GROUP>() {
-      wave_stream<U>(row, s0, s1, [&](int c0, const float (&x)[U]) {
+      wave_stream<U>(row, s0, s1, [&](uint32_t c0, const float (&x)[U]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           // (bool & bool: a short-circuit && would branch)
@@ -545,7 +545,7 @@ __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k,
       uint32_t hk = prefix | ~pmask;
       hk = hk > 0xFF800000u ? 0xFF800000u : hk == 0x7FFFFFFFu ? 0x7FFFFFFEu : hk;
       const float lo = ord_inv(lk), hi = ord_inv(hk);
-      wave_stream<U>(row, s0, s1, [&](int c0, const float (&x)[U]) {
+      wave_stream<U>(row, s0, s1, [&](uint32_t c0, const float (&x)[U]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const bool in = (c0 + u * kWave + l < s1) & (x[u] >= lo) & (x[u] <= hi);
@@ -617,10 +617,10 @@ __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k,
   // "not NaN" and key == K* is "NaN"
   const float kf = ord_inv(kstar);
   auto write_pass = [&]<bool KNAN>() {
-    wave_stream<U>(row, s0, s1, [&](int c0, const float (&x)[U]) {
+    wave_stream<U>(row, s0, s1, [&](uint32_t c0, const float (&x)[U]) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int i = c0 + u * kWave + l;
+        const uint32_t i = c0 + u * kWave + l;
         const bool v = i < s1;
         const bool gt = v & (KNAN ? x[u] == x[u] : x[u] > kf), eq = v & (KNAN ? x[u] != x[u] : x[u] == kf);
         const uint64_t mg = __ballot(gt), me = __ballot(eq);

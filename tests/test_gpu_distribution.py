@@ -159,3 +159,35 @@ def test_union_spans(lib, nq, k, group, span, top):
     np.testing.assert_array_equal(c.cpu().numpy(), rc)
     np.testing.assert_array_equal(u.cpu().numpy(), ru)
     np.testing.assert_array_equal(m.cpu().numpy().view(np.uint32), rm)
+
+
+# rows of nearly 2^31 keys, whose last steps pass the largest 32-bit position:
+# planted keys (some at the very end), tied background keys below them, k
+# within the planted ones and past them
+@pytest.mark.parametrize("nk", [2 ** 31 - 1, 2 ** 31 - 20000])
+def test_rows_of_2_to_the_31_keys(lib, nk):
+    scores = torch.empty(1, 2 ** 31, dtype=torch.float32, device="cuda")
+    scores.view(-1, 1024)[:] = -1.0 - torch.arange(1024, device="cuda") / 1024.0
+    rng = np.random.default_rng(1)
+    at = np.unique(np.concatenate([rng.integers(0, nk, size=400), np.arange(nk - 100, nk)]))
+    vals = (10.0 + np.arange(len(at))).astype(np.float32)
+    rng.shuffle(vals)
+    scores[0, torch.from_numpy(at).cuda()] = torch.from_numpy(vals).cuda()
+    order = np.argsort(-vals)
+    free = np.setdiff1d(np.arange(0, 2 ** 20, 1024), at)  # background keys of score -1, in order
+
+    def check(i, s, k):
+        n = min(k, len(at))
+        np.testing.assert_array_equal(i.cpu().numpy()[0, :n], at[order[:n]])
+        np.testing.assert_array_equal(s.cpu().numpy()[0, :n], vals[order[:n]])
+        np.testing.assert_array_equal(i.cpu().numpy()[0, n:], free[:k - n])
+        assert bool((s[0, n:] == -1.0).all())
+
+    check(*lt.topk_radix(scores, 40, nk, sorted_output=True), 40)
+    check(*lt.topk_radix(scores, 600, nk, sorted_output=True), 600)
+    sample = torch.from_numpy(np.sort(at[:300]).astype(np.int32)).cuda()
+    for splits in (0, 1):
+        o = lt.make_options(sorted_output=True, sample_keys=sample, key_splits=splits)
+        check(*lt.topk_select(scores, 40, nk, options=o), 40)
+    o = lt.make_options(sorted_output=True, force_fallback=True)
+    check(*lt.topk_select(scores, 600, nk, options=o), 600)
