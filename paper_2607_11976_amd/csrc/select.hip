@@ -167,7 +167,9 @@ __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride,
   // the lowest bin that the histogram takes
   int from = 0;
   if constexpr (HOLD > 0) {
-    const float hi = (float)(m - m / 4), mid = (float)(m / 2);
+    // (bins end at m - 1: the greatest scores, at m and above, are clamped to it)
+    const int b_hi = min(m - m / 4, m - 1), b_mid = m / 2;
+    const float hi = (float)b_hi, mid = (float)b_mid;
     uint32_t n_hi = 0, n_mid = 0;
     each(false, [&](const float* x) {
 #pragma unroll
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride,
       atomicAdd(&sel[1], n_mid);
     }
     __syncthreads();
-    from = sel[0] >= (uint32_t)k ? m - m / 4 : sel[1] >= (uint32_t)k ? m / 2 : 0;
+    from = sel[0] >= (uint32_t)k ? b_hi : sel[1] >= (uint32_t)k ? b_mid : 0;
   }
   each(false, [&](const float* x) {
 #pragma unroll

@@ -143,3 +143,27 @@ def test_grouped_ties_go_to_the_lower_key(lib, layout, opt):
             kept = np.sort(fi[t][fs[t] == kth])
             np.testing.assert_array_equal(kept, tied[: kept.size])
         assert np.mean([np.sum(dn[t] == fs[t, k - 1]) > 1 for t in range(cfg.nq)]) > 0.5, "too few ties"
+
+
+# the sample's initial bin: the bin of its k-th score, also with so few bins
+# that the top quarter of them is no whole bin, and with ties at the maximum
+@pytest.mark.parametrize("num_bins", [1, 2, 3, 4, 5, 256])
+@pytest.mark.parametrize("k", [1, 3, 40])
+@pytest.mark.parametrize("nq,ns", [(5, 120), (520, 300)])
+def test_initial_bin(lib, num_bins, k, nq, ns):
+    nk = 3000
+    scores = workloads.score_rows(nq, nk, seed=nq + k, kind="normal")
+    rng = np.random.default_rng(ns)
+    keys = np.sort(rng.choice(nk, size=ns, replace=False)).astype(np.int32)
+    scores[:, torch.from_numpy(keys[:4]).long()] = 9.0  # four sample keys at the maximum
+    scores[2, :] = 1.0                                  # one value: delta = 1, c = -1
+    stats = torch.full((nq, lt.LT_ROW_STATS), -7, dtype=torch.int32, device="cuda")
+    lt.topk_select(scores.cuda(), k, nk, options=lt.make_options(
+        row_stats=stats, num_bins=num_bins, sample_keys=torch.from_numpy(keys).cuda()))
+    st = stats.cpu().numpy()
+    sample = scores.numpy()[:, keys]
+    for t in sorted({0, 1, 2, nq - 1}):
+        delta, c = st[t, 6:8].view(np.float32)
+        b = np.sort(bins_of(sample[t], delta, c, num_bins))[::-1]
+        assert st[t, 8] == num_bins and st[t, 9] == ns
+        assert st[t, 4] == b[k - 1], (t, st[t, 4], b[k - 1])
