@@ -1760,7 +1760,7 @@ hipError_t launch_fused_fallback(const ScoreArgs& a, int k, uint32_t flags, uint
   hipError_t err = hipErrorInvalidValue;
   with_cfg(a.dtype, a.mode, a.h, a.d, a.w == nullptr, [&]<class C>() {
     size_t lds = C::SCAN_LDS;
-    const size_t rl = radix_lds_bytes(k);
+    const size_t rl = radix_lds_bytes(C::NTHREADS, k);
     if (rl > lds) lds = rl;
     const size_t meta = (lds + 15) & ~(size_t)15;
     lds = meta + fallback_meta_lds<C>();

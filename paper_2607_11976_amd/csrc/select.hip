@@ -1072,8 +1072,8 @@ struct RadixRow {
 // then the sort slots and buckets) and 64 words of exchange; at least what
 // radix_select_row needs.
 constexpr size_t kRadixExchange = 64 * 4;
-static size_t radix_row_lds(int k, int E) {
-  const size_t a = kRadixExchange + (size_t)E * 8, b = radix_lds_bytes(k);
+static size_t radix_row_lds(int nth, int k, int E) {
+  const size_t a = kRadixExchange + (size_t)E * 8, b = radix_lds_bytes(nth, k);
   return a > b ? a : b;
 }
 
@@ -1344,10 +1344,10 @@ hipError_t launch_fallback_scores(const float* scores, int64_t stride, int nk, c
                                   const int32_t* starts, int k, uint32_t flags, uint32_t* qctl,
                                   const int32_t* queue, int32_t* cidx, float* cscore, int32_t* out_i, float* out_s,
                                   int grid, hipStream_t st) {
-  if (radix_lds_bytes(k) > 65536)
-    (void)hipFuncSetAttribute((const void*)k_fallback_scores, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)radix_lds_bytes(k));
-  hipLaunchKernelGGL(k_fallback_scores, dim3(grid), dim3(kSelThreads), radix_lds_bytes(k), st, scores,
+  const size_t lds = radix_lds_bytes(kSelThreads, k);
+  if (lds > 65536)
+    (void)hipFuncSetAttribute((const void*)k_fallback_scores, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL(k_fallback_scores, dim3(grid), dim3(kSelThreads), lds, st, scores,
                      stride, nk, offs, starts, k, flags, qctl, queue, cidx, cscore, out_i, out_s);
   return hipGetLastError();
 }
@@ -1356,7 +1356,7 @@ hipError_t launch_fallback_rows(const uint32_t* qctl, const int32_t* fbflag, con
                                 const int32_t* offs, const int32_t* starts, int k, uint32_t flags, int slots,
                                 int qt, int32_t* out_i, float* out_s, hipStream_t st) {
   if (!may_dense(nq, slots, qt)) return hipSuccess;
-  const size_t lds = radix_lds_bytes(k);
+  const size_t lds = radix_lds_bytes(kSelThreads, k);
   if (lds > 65536)
     (void)hipFuncSetAttribute((const void*)k_fallback_rows, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(k_fallback_rows, dim3(nq), dim3(kSelThreads), lds, st, qctl, fbflag, scratch, nq, nk, offs,
@@ -1367,8 +1367,8 @@ hipError_t launch_fallback_rows(const uint32_t* qctl, const int32_t* fbflag, con
 hipError_t launch_radix(const float* scores, int64_t stride, int nq, int nk, const int32_t* offs,
                         int k, uint32_t flags, int32_t* out_i, float* out_s, hipStream_t st) {
   const int E = max(4096, 2 * next_pow2(k));
-  const size_t lds = radix_row_lds(k, E);
   auto go = [&](auto kernel, int nth) {
+    const size_t lds = radix_row_lds(nth, k, E);
     if (lds > 65536) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kernel, dim3(nq), dim3(nth), lds, st, scores, stride, nk, offs, k, E, flags, out_i, out_s);
   };

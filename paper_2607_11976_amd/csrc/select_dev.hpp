@@ -214,12 +214,14 @@ __device__ __forceinline__ bool order_entries(int2* e2, uint32_t n, float mn, fl
   return true;
 }
 
-// LDS layout of radix_select_row: a 256-bin histogram per wave (up to
-// kRadixWaves waves), their sum, 64 words of exchange, then the sort entries.
-constexpr int kRadixWaves = 16;
-constexpr size_t kRadixTot = (size_t)kRadixWaves * 256 * 4;
-constexpr size_t kRadixTmp = kRadixTot + 256 * 4;
-constexpr size_t kRadixEnt = kRadixTmp + 64 * 4;
+// LDS layout of radix_select_row with nth threads: a 256-bin histogram per
+// wave, their sum, 64 words of exchange, then the sort entries. (Two blocks of
+// up to 512 threads per CU also with the 8192 entries of k > 4096: with room
+// for 16 waves whatever the block, 1000 rows of 32768 scores, k = 5000, forced
+// to the fallback took 1012 us, sorted, and 333 unsorted; they take 599 and 235.)
+__host__ __device__ constexpr size_t radix_tot(int nth) { return (size_t)(nth / kWave) * 256 * 4; }
+__host__ __device__ constexpr size_t radix_tmp(int nth) { return radix_tot(nth) + 256 * 4; }
+__host__ __device__ constexpr size_t radix_ent(int nth) { return radix_tmp(nth) + 64 * 4; }
 
 // Sort entries of radix_select_row: the output sort (k of them) and the keys
 // of a digit prefix gathered in LDS once at most this many remain.
@@ -227,10 +229,11 @@ __host__ __device__ __forceinline__ int radix_collect_cap(int k) {
   const int p = next_pow2(k);
   return p < 4096 ? 4096 : p;
 }
-// LDS bytes radix_select_row needs for a given k.
-__host__ __device__ __forceinline__ size_t radix_lds_bytes(int k) {
-  return kRadixEnt + (size_t)radix_collect_cap(k) * 8;
+// LDS bytes radix_select_row needs with nth threads for a given k.
+__host__ __device__ __forceinline__ size_t radix_lds_bytes(int nth, int k) {
+  return radix_ent(nth) + (size_t)radix_collect_cap(k) * 8;
 }
+static_assert(2 * (radix_ent(512) + (size_t)LT_K_MAX * 8) <= 160 * 1024, "two blocks per CU at every k");
 
 // Sort the first n (<= k) entries of an output row by the total order, in
 // place. The rows were written by this block; the caller has made them
@@ -393,7 +396,7 @@ __device__ __forceinline__ void wave_stream(const float* row, uint32_t s0, uint3
 template <int NTH>
 __device__ __noinline__ void radix_copy_short_row(const float* row, int n, int k, int32_t* oi, float* os, bool sorted,
                                                   uint8_t* lds, bool pad) {
-  uint64_t* ent = reinterpret_cast<uint64_t*>(lds + kRadixEnt);
+  uint64_t* ent = reinterpret_cast<uint64_t*>(lds + radix_ent(NTH));
   const int tid = threadIdx.x;
   auto fetch = [&](uint32_t idx) { return row[idx]; };
   for (int i = tid; i < k; i += NTH) {
@@ -418,7 +421,7 @@ template <int NTH>
 __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k, int32_t* oi, float* os, bool sorted,
                                                  uint8_t* lds, bool pad) {
   constexpr int NW = NTH / kWave, U = kRadixUnroll;
-  static_assert(NW <= kRadixWaves, "one histogram per wave");
+  static_assert(NW <= 16, "16 words of exchange per wave count");
   static_assert(NW >= 4, "segments of fewer than 2^30 keys");
   // the sizes and flags are the same in every lane (arguments arrive in
   // vector registers): branches on them stay scalar, which keeps the loads
@@ -428,9 +431,9 @@ __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k,
   sorted = __builtin_amdgcn_readfirstlane((int)sorted) != 0;
   pad = __builtin_amdgcn_readfirstlane((int)pad) != 0;
   uint32_t* hist = reinterpret_cast<uint32_t*>(lds);              // [NW][256]
-  uint32_t* tot = reinterpret_cast<uint32_t*>(lds + kRadixTot);   // [256]
-  uint32_t* tmp = reinterpret_cast<uint32_t*>(lds + kRadixTmp);   // [64]
-  uint64_t* ent = reinterpret_cast<uint64_t*>(lds + kRadixEnt);
+  uint32_t* tot = reinterpret_cast<uint32_t*>(lds + radix_tot(NTH));   // [256]
+  uint32_t* tmp = reinterpret_cast<uint32_t*>(lds + radix_tmp(NTH));   // [64]
+  uint64_t* ent = reinterpret_cast<uint64_t*>(lds + radix_ent(NTH));
   const int tid = threadIdx.x, l = lane_id(), wave = tid / kWave;
   uint32_t* hw = hist + wave * 256;
   auto fetch = [&](uint32_t idx) { return row[idx]; };

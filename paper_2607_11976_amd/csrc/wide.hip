@@ -719,7 +719,7 @@ hipError_t launch_wide_fallback(const ScoreArgs& a, int k, uint32_t flags, uint3
   hipError_t err = hipErrorInvalidValue;
   with_wide(a.dtype, a.mode, a.h, a.d, [&]<class C>() {
     size_t lds = C::Q_LDS;
-    const size_t rl = radix_lds_bytes(k);
+    const size_t rl = radix_lds_bytes(C::NTHREADS, k);
     if (rl > lds) lds = rl;
     allow_lds(k_wide_fallback<C>, lds);
     hipLaunchKernelGGL(k_wide_fallback<C>, dim3(kFallbackGrid), dim3(C::NTHREADS), lds, st, a, k, flags, qctl,
