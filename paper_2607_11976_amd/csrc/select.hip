@@ -54,7 +54,7 @@ __device__ __forceinline__ void range_load(const float* rp, const int32_t* list,
 }
 
 // HOLD: sample scores per thread kept in registers (ns <= NTH * HOLD), or 0:
-// read twice. The histogram takes only what tau0 needs of it: the bins from
+// read twice. The histogram of held scores takes only what tau0 needs of it: the bins from
 // 3m/4 up where they hold k sample keys, else from m/2 up, else all (LDS
 // atomics on the few bins that most scores fall in cost more than the reads).
 template <int NTH, bool FROM_SCORES, int HOLD>
@@ -123,23 +123,34 @@ __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride,
           body(v + j);
         }
       }
-    } else {
-      for (int base = 0; base < ns; base += STEP) {
-        fetch(base, v, first);
-        body(v);
-      }
     }
   };
   float mn = __builtin_inff(), mx = -__builtin_inff();
-  each(true, [&](const float* x) {
+  if constexpr (HOLD > 0) {
+    each(true, [&](const float* x) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (__builtin_isfinite(x[u])) {
-        mn = fminf(mn, x[u]);
-        mx = fmaxf(mx, x[u]);
+      for (int u = 0; u < U; ++u) {
+        if (__builtin_isfinite(x[u])) {
+          mn = fminf(mn, x[u]);
+          mx = fmaxf(mx, x[u]);
+        }
+      }
+    });
+  } else {
+    for (int base = 0; base < ns; base += STEP) {
+      float s[U];
+      bool vis[U];
+      range_load<NTH, FROM_SCORES>(rp, list, ns, rr, base, s, vis);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        nvis += vis[u];
+        if (vis[u] && __builtin_isfinite(s[u])) {
+          mn = fminf(mn, s[u]);
+          mx = fmaxf(mx, s[u]);
+        }
       }
     }
-  });
+  }
   mn = wave_min(mn);
   mx = wave_max(mx);
   nvis = wave_sum(nvis);
@@ -188,13 +199,26 @@ __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride,
     __syncthreads();
     from = sel[0] >= (uint32_t)k ? b_hi : sel[1] >= (uint32_t)k ? b_mid : 0;
   }
-  each(false, [&](const float* x) {
+  if constexpr (HOLD > 0) {
+    each(false, [&](const float* x) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int b = bin_of(bin_x(x[u], delta, c), m);
-      if (b >= from) atomicAdd(&hist[b], 1u);
+      for (int u = 0; u < U; ++u) {
+        const int b = bin_of(bin_x(x[u], delta, c), m);
+        if (b >= from) atomicAdd(&hist[b], 1u);
+      }
+    });
+  } else {
+    for (int base = 0; base < ns; base += STEP) {
+      float s[U];
+      bool vis[U];
+      range_load<NTH, FROM_SCORES>(rp, list, ns, rr, base, s, vis);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int b = bin_of(bin_x(s[u], delta, c), m);
+        if (vis[u] && b >= 0) atomicAdd(&hist[b], 1u);
+      }
     }
-  });
+  }
   __syncthreads();
   if (wave == 0) {
     const int tau0 = wave_threshold(hist, m, (uint32_t)k, nullptr);
@@ -1261,16 +1285,20 @@ hipError_t launch_range(bool from_scores, const float* src, int64_t stride, int 
   };
   // a long sample is read in fewer, wider steps (the kernel waits on loads);
   // so are the rows of a launch of few rows, which otherwise leaves most of
-  // the GPU idle
+  // the GPU idle. The scores stay in registers as long as they fit (12288
+  // samples of 3000 rows: 40 us, 51 us read twice), but 64 of them in 1024
+  // threads take a whole CU: many rows whose list is read too (40000 samples
+  // of 1500 rows, causal: 106 us held, 88 us read twice) read them twice
   const bool large = ns >= kRangeLargeSample || nq <= kSelFewRows;
   auto by_size = [&](auto FROM) {
     constexpr bool F = decltype(FROM)::value;
     if (!large && ns <= kRangeThreads * kRangeHold) go(k_range<kRangeThreads, F, kRangeHold>, kRangeThreads);
-    else if (!large) go(k_range<kRangeThreads, F, 0>, kRangeThreads);
+    else if (!large) go(k_range<kRangeThreads, F, 2 * kRangeHold>, kRangeThreads);
     else if (ns <= kRangeThreadsLarge * kRangeHoldFew) go(k_range<kRangeThreadsLarge, F, kRangeHoldFew>, kRangeThreadsLarge);
     else if (nq > kSelFewRows && ns <= kRangeThreadsMid * 2 * kRangeHold) go(k_range<kRangeThreadsMid, F, 2 * kRangeHold>, kRangeThreadsMid);
     else if (ns <= kRangeThreadsLarge * kRangeHold) go(k_range<kRangeThreadsLarge, F, kRangeHold>, kRangeThreadsLarge);
-    else if (ns <= kRangeThreadsLarge * 2 * kRangeHold) go(k_range<kRangeThreadsLarge, F, 2 * kRangeHold>, kRangeThreadsLarge);
+    else if (ns <= kRangeThreadsLarge * 2 * kRangeHold && (F || !list || nq <= kSelFewRows))
+      go(k_range<kRangeThreadsLarge, F, 2 * kRangeHold>, kRangeThreadsLarge);
     else go(k_range<kRangeThreadsLarge, F, 0>, kRangeThreadsLarge);
   };
   if (from_scores) by_size(std::true_type{});

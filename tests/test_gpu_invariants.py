@@ -167,3 +167,34 @@ def test_initial_bin(lib, num_bins, k, nq, ns):
         b = np.sort(bins_of(sample[t], delta, c, num_bins))[::-1]
         assert st[t, 8] == num_bins and st[t, 9] == ns
         assert st[t, 4] == b[k - 1], (t, st[t, 4], b[k - 1])
+
+
+# samples read twice, held by 256, 512 or 1024 threads (at the last length of
+# each), with a list to read (causal) and without: the initial bin against the
+# sample's own scores
+@pytest.mark.parametrize("nq", [5, 520])
+@pytest.mark.parametrize("ns", [8192, 8193, 16383, 16384, 32769, 65537])
+@pytest.mark.parametrize("causal", [False, True])
+def test_initial_bin_of_long_samples(lib, nq, ns, causal):
+    nk, k = (70000 if ns <= 32768 else ns), 500
+    x = workloads.exact_inputs(nq, nk, 4, 128, "bf16", seed=ns, causal=False)
+    d = to_dev(x)
+    rng = np.random.default_rng(ns + nq)
+    offs = rng.integers(nk // 2, nk + 1, size=nq).astype(np.int32) if causal else None
+    ends = None if offs is None else torch.from_numpy(offs).cuda()
+    stats = torch.full((nq, lt.LT_ROW_STATS), -7, dtype=torch.int32, device="cuda")
+    if ns <= 32768:  # a caller's list
+        keys = np.sort(rng.choice(nk, size=ns, replace=False)).astype(np.int32)
+        args = dict(sample_keys=torch.from_numpy(keys).cuda())
+    else:            # every key
+        keys = np.arange(nk)
+        args = dict(sample_size=nk)
+    lt.indexer_topk(d["q"], d["w"], d["keys"], k, ends, options=lt.make_options(row_stats=stats, **args))
+    dense = lt.indexer_scores(d["q"], d["w"], d["keys"]).cpu().numpy()
+    st = stats.cpu().numpy()
+    for t in (0, nq // 2, nq - 1):
+        s = dense[t, keys[keys < offs[t]] if causal else keys]
+        delta, c = st[t, 6:8].view(np.float32)
+        assert st[t, 9] == len(s)
+        b = np.sort(bins_of(s, delta, c, st[t, 8]))[::-1]
+        assert st[t, 4] == b[k - 1], (t, st[t, 4], b[k - 1])
