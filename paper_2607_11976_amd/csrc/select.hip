@@ -456,8 +456,7 @@ constexpr size_t select_ent_offset(int nth) { return ((size_t)kMaxBins + 32 + nt
 // order_entries, where a gather in list order, block-wide step by step, and a
 // bitonic sort took twice as long (4096 rows of 8.7 K candidates, k = 2048:
 // 314 -> 149 us; 10000 rows of 1.1 K, k = 100: 231 -> 125 us).
-// Rows that order_entries does not take, or with more than sort_slots(E) keys,
-// take the general path, whose sort does not depend on the values.
+// Rows with more than sort_slots(E) keys take the general path.
 //
 // nmax: keys at or above bin tau by the histograms. Returns 0 when the row is
 // written, 1 when the lists disagree with the histograms (the fallback's), -1
@@ -566,7 +565,7 @@ __device__ __forceinline__ int select_sorted(int row, const RowParam& p, const u
     mx = fmaxf(mx, red[NW + w]);
   }
 
-  if (!order_entries<NTH, EPT>(e2, n, mn, mx, bk, NB, off)) return -1;
+  order_entries<NTH, EPT>(e2, n, mn, mx, bk, NB, off);
   for (int i = tid; i < k; i += NTH) {
     const bool v = (uint32_t)i < n;
     const int2 x = v ? e2[i] : make_int2(-1, __float_as_int(-__builtin_inff()));
@@ -1048,11 +1047,16 @@ __global__ __launch_bounds__(kSelThreads) void k_fallback_scores(
 // at a time: after the least and greatest key are known, a histogram of 4096
 // equal parts of the span gives the part that holds the k-th key, and that
 // part is cut again until it and the keys above it fit in LDS (one histogram,
-// usually). They are then gathered there and ordered by order_entries: three
-// passes over the row, the later ones from the caches.
+// usually), or until it is one key, whose copies are then cut by index. What
+// is kept is gathered in LDS and ordered by order_entries: three passes over
+// the row, the later ones from the caches.
 // Bound by those passes at one block per CU and by the histogram's LDS atomics:
 // 255 rows of 65501 scores, k = 2048, take 49 us, against 224 us with four
-// 8-bit digits in 256-thread blocks. Rows with too many equal keys at the k-th go to radix_select_row.
+// 8-bit digits in 256-thread blocks. 512 rows of 65536, k = 2048: 94 us of
+// normal scores, 101 of scores spread over 50 octaves, 172 of multiples of
+// 1/8, 193 of zeros but for one in 500 (228, 271 and 813 when such rows were
+// given up and done again by radix_select_row, which takes 147, 184 and 457
+// from the start).
 // ---------------------------------------------------------------------------
 constexpr int kRadixBits = 12;
 constexpr int kRadixThreads = 1024, kRadixThreadsSmall = 256;
@@ -1143,45 +1147,98 @@ __device__ __forceinline__ bool radix_row(const float* rowp, int n, int k, int E
     hi = max(hi, tmp[NW + w]);
   }
   // ---- the part that holds the k-th key ----
-  uint32_t remaining = (uint32_t)k, above = 0, count;
-  for (;;) {
-    const uint32_t span = hi - lo;
-    const int shift = span < (uint32_t)BINS ? 0 : 32 - kRadixBits - __builtin_clz(span);
+  // (the parts lie above the least key, which is not counted but left over: a
+  // masked row's -inf, or the zeros of a sparse one, would all wait for one LDS
+  // word, and a row whose k-th key it is ends here)
+  uint32_t remaining = (uint32_t)k, above = 0, count, part = (uint32_t)n;  // part: keys in [lo, hi]
+  // thread t owns Q bins, from the top (the histogram of keys) or the bottom
+  uint32_t sum, tot;
+  auto scan_bins = [&](const uint32_t* first, int dir) {
+    sum = 0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) sum += first[dir * i];
+    return block_scan_excl<NTH>(sum, tmp, &tot);
+  };
+  auto clear_bins = [&]() {
     __syncthreads();  // the exchange words and the histogram have been read
     for (int b = tid; b < BINS; b += NTH) hist[b] = 0u;
     __syncthreads();
-    rr.each([&](int i0, const float* x) {
+  };
+  for (;;) {
+    const uint32_t low = lo + 1u, span = hi - lo;
+    const int shift = span <= (uint32_t)BINS ? 0 : 32 - kRadixBits - __builtin_clz(span - 1u);
+    clear_bins();
+    if (span > 0)
+      rr.each([&](int i0, const float* x) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t o = ord_key(x[u]) - lo;
-        if ((i0 + u * NTH + tid < rr.n) & (o <= span)) atomicAdd(&hist[o >> shift], 1u);
-      }
-    });
+        for (int u = 0; u < U; ++u) {
+          const uint32_t o = ord_key(x[u]) - low;
+          if ((i0 + u * NTH + tid < rr.n) & (o < span)) atomicAdd(&hist[o >> shift], 1u);
+        }
+      });
     __syncthreads();
-    // descending: thread t owns bins BINS - 1 - t * Q and the Q - 1 below
-    uint32_t h[Q], sum = 0, tot;
-#pragma unroll
-    for (int i = 0; i < Q; ++i) sum += h[i] = hist[BINS - 1 - (tid * Q + i)];
-    uint32_t at = block_scan_excl<NTH>(sum, tmp, &tot);
+    const uint32_t* own = hist + BINS - 1 - tid * Q;
+    uint32_t at = scan_bins(own, -1);
+    if (remaining > tot) {  // block-uniform
+      above += tot;
+      remaining -= tot;
+      count = above + part - tot;
+      break;
+    }
     if (at < remaining && remaining <= at + sum) {  // one thread
 #pragma unroll
       for (int i = 0; i < Q; ++i) {
-        if (at < remaining && remaining <= at + h[i]) {
+        const uint32_t c = own[-i];
+        if (at < remaining && remaining <= at + c) {
           tmp[48] = (uint32_t)(BINS - 1 - (tid * Q + i));
           tmp[49] = at;
-          tmp[50] = h[i];
+          tmp[50] = c;
         }
-        at += h[i];
+        at += c;
       }
     }
     __syncthreads();
     above += tmp[49];
     remaining -= tmp[49];
-    count = above + tmp[50];
-    lo += tmp[48] << shift;
-    if (count <= slots) break;
-    if (shift == 0) return false;
+    part = tmp[50];
+    count = above + part;
+    lo = low + (tmp[48] << shift);
+    if (count <= slots || shift == 0) break;
     hi = lo + ((1u << shift) - 1u);
+  }
+  // More keys equal to the k-th than there is room for: those of the lowest
+  // indices, up to the end of the 64 (or n / 4096) that hold the last of them.
+  uint32_t limit = UINT_MAX;
+  if (count > slots) {
+    const uint32_t last = (uint32_t)rr.n - 1u;
+    const int shift = max(6, 32 - kRadixBits - __builtin_clz(last | 1u));
+    clear_bins();
+    rr.each([&](int i0, const float* x) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t i = (uint32_t)(i0 + u * NTH + tid);
+        const uint64_t eq = __ballot((i <= last) & (ord_key(x[u]) == lo));
+        if (l == 0 && eq != 0) atomicAdd(&hist[i >> shift], (uint32_t)__popcll(eq));
+      }
+    });
+    __syncthreads();
+    const uint32_t* own = hist + tid * Q;
+    uint32_t at = scan_bins(own, 1);
+    if (at < remaining && remaining <= at + sum) {  // one thread
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        const uint32_t c = own[i];
+        if (at < remaining && remaining <= at + c) {
+          tmp[48] = (uint32_t)(tid * Q + i + 1) << shift;
+          tmp[49] = at + c;
+        }
+        at += c;
+      }
+    }
+    __syncthreads();
+    limit = tmp[48];
+    count = above + tmp[49];
+    if (count > slots) return false;
   }
   // ---- the keys from `lo` up ----
   const int NB = bucket_count<NTH>(count, E);
@@ -1190,11 +1247,13 @@ __device__ __forceinline__ bool radix_row(const float* rowp, int n, int k, int E
   if (tid == 0) tmp[48] = 0u;
   __syncthreads();
   float mn = __builtin_inff(), mx = -__builtin_inff();
-  rr.each([&](int i0, const float* x) {
+  auto gather = [&]<bool CUT>(int i0, const float* x) {
     uint32_t in = 0u, nin = 0u;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool i1 = (i0 + u * NTH + tid < rr.n) & (ord_key(x[u]) >= lo);
+      const uint32_t o = ord_key(x[u]);
+      const int i = i0 + u * NTH + tid;
+      const bool i1 = (i < rr.n) & (CUT ? (o > lo) | ((o == lo) & ((uint32_t)i < limit)) : o >= lo);
       in |= (uint32_t)i1 << u;
       nin += (uint32_t)__popcll(__ballot(i1));
     }
@@ -1216,7 +1275,9 @@ __device__ __forceinline__ bool radix_row(const float* rowp, int n, int k, int E
       }
       r += (uint32_t)__popcll(mk);
     }
-  });
+  };
+  if (limit == UINT_MAX) rr.each([&](int i0, const float* x) { gather.template operator()<false>(i0, x); });
+  else rr.each([&](int i0, const float* x) { gather.template operator()<true>(i0, x); });
   mn = wave_min(mn);
   mx = wave_max(mx);
   float* red = reinterpret_cast<float*>(tmp);
@@ -1230,7 +1291,7 @@ __device__ __forceinline__ bool radix_row(const float* rowp, int n, int k, int E
     mn = fminf(mn, red[w]);
     mx = fmaxf(mx, red[NW + w]);
   }
-  if (!order_entries<NTH, EPT>(e2, count, mn, mx, bk, NB, tmp)) return false;
+  order_entries<NTH, EPT>(e2, count, mn, mx, bk, NB, tmp);
   for (int i = tid; i < k; i += NTH) {
     oi[i] = e2[i].x;
     os[i] = __int_as_float(e2[i].y);
@@ -1239,7 +1300,7 @@ __device__ __forceinline__ bool radix_row(const float* rowp, int n, int k, int E
 }
 
 template <int NTH>
-__global__ __launch_bounds__(NTH) void k_radix(const float* scores, int64_t stride, int nk, const int32_t* offs, int k,
+__global__ __launch_bounds__(NTH, 4) void k_radix(const float* scores, int64_t stride, int nk, const int32_t* offs, int k,
                                                int E, uint32_t flags, int32_t* out_i, float* out_s) {
   extern __shared__ __align__(16) uint8_t lds[];
   const int row = blockIdx.x;

@@ -127,14 +127,16 @@ __host__ __device__ __forceinline__ int next_pow2(int n) {
 
 // ---------------------------------------------------------------------------
 // Ordering of up to sort_slots(E) (key, score) entries in LDS by the total
-// order, with one distribution pass: a linear map of the score over [mn, mx]
-// into NB buckets (any map that does not decrease with the score will do; NaN
-// and -inf take the lowest), a suffix sum of the bucket counts, and a rank
-// within the bucket by comparing its few keys. Eight barriers and O(1) LDS
-// operations per key for spread scores, where a bitonic sort of 2048 keys
-// takes 66 stages.
+// order, with one distribution pass: a map that does not decrease with the
+// score into NB buckets, a suffix sum of the bucket counts, and a rank within
+// the bucket by comparing its few keys. Eight barriers and O(1) LDS operations
+// per key for spread scores, where a bitonic sort of 2048 keys takes 66 stages.
+// The map is linear in the score over [mn, mx] (NaN and -inf take the lowest
+// bucket); where that leaves a bucket of more than kBucketMax keys, linear in
+// the order key (scores spread over many octaves). Entries that neither
+// spreads (many equal scores) are sorted where they are, by a bitonic network.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kBucketMax = 128;  // a bucket with more keys (many equal scores): not this way
+constexpr uint32_t kBucketMax = 128;
 // A buffer of E 8-byte entries holds the slots and, after them, the buckets.
 __host__ __device__ constexpr int sort_buckets(int E) { return E / 2; }    // 4 bytes each
 __host__ __device__ constexpr int sort_slots(int E) { return E - E / 4; }  // 8 bytes each
@@ -145,49 +147,75 @@ __device__ __forceinline__ int bucket_count(uint32_t n, int E) {
   return min(sort_buckets(E), max(NTH, next_pow2((int)n)));
 }
 
-// e2[0, n): the entries, n <= NTH * EPT, rewritten in order; mn, mx: the least
-// and greatest finite score (inf, -inf: none), the same in every thread;
-// bk[0, NB): zeroed, NB a multiple of NTH; tmp: NTH / kWave words. All of it
-// made visible by a barrier. Returns false, in every thread and with e2 as it
-// was, when a bucket holds more than kBucketMax entries. Ends with a barrier.
+// An entry in the total order, the raw score bits kept.
+struct OrderedEntry {
+  int key, score;
+  __device__ __forceinline__ bool operator<(const OrderedEntry& o) const {
+    return comp_key(__int_as_float(score), (uint32_t)key) < comp_key(__int_as_float(o.score), (uint32_t)o.key);
+  }
+};
+
+// e2[0, n): the entries, n <= sort_slots(E) and NTH * EPT, rewritten in order;
+// mn, mx: the least and greatest finite score (inf, -inf: none), the same in
+// every thread; bk[0, NB), at e2 + sort_slots(E): zeroed, NB a multiple of NTH;
+// tmp: NTH / kWave words. All of it made visible by a barrier. Ends with a
+// barrier.
 template <int NTH, int EPT>
-__device__ __forceinline__ bool order_entries(int2* e2, uint32_t n, float mn, float mx, uint32_t* bk, int NB,
+__device__ __forceinline__ void order_entries(int2* e2, uint32_t n, float mn, float mx, uint32_t* bk, int NB,
                                               uint32_t* tmp) {
   const int tid = threadIdx.x;
-  float scale = (float)NB / (mx - mn);
-  if (!(scale > 0.0f) || !__builtin_isfinite(scale)) scale = 0.0f;
   const float top = (float)(NB - 1);
+  const int Q = NB / NTH;
   int2 e[EPT];
   uint32_t bs[EPT];  // bucket << 16 | slot in the bucket, later the place in the order
+  // false when a bucket holds more than kBucketMax entries
+  auto spread = [&]<bool BY_KEY>() {
+    const uint32_t omn = ord_key(mn);
+    float scale = (float)NB / (BY_KEY ? (float)(ord_key(mx) - omn) : mx - mn);
+    if (!(scale > 0.0f) || !__builtin_isfinite(scale)) scale = 0.0f;
 #pragma unroll
-  for (int j = 0; j < EPT; ++j) {
-    const uint32_t i = (uint32_t)(tid + j * NTH);
-    if (i < n) {
-      e[j] = e2[i];
-      const float sc = __int_as_float(e[j].y);
-      const float t = fmaxf(fminf((sc - mn) * scale, top), 0.0f);
-      const uint32_t b = scale > 0.0f && sc == sc ? (uint32_t)t : 0u;
-      bs[j] = b << 16 | atomicAdd(&bk[b], 1u);
+    for (int j = 0; j < EPT; ++j) {
+      if ((uint32_t)(tid + j * NTH) < n) {
+        if (!BY_KEY) e[j] = e2[tid + j * NTH];
+        const float sc = __int_as_float(e[j].y);
+        const float d = BY_KEY ? (float)(ord_key(sc) - omn) : sc - mn;
+        const float t = fmaxf(fminf(d * scale, top), 0.0f);
+        const uint32_t b = scale > 0.0f && sc >= mn ? (uint32_t)t : 0u;
+        bs[j] = b << 16 | atomicAdd(&bk[b], 1u);
+      }
+    }
+    __syncthreads();
+    uint32_t sum = 0, big = 0;
+    for (int i = 0; i < Q; ++i) {
+      const uint32_t c = bk[NB - 1 - (tid * Q + i)];
+      sum += c;
+      big = max(big, c);
+    }
+    // bk[b]: start of the bucket in descending order << 16 | its count
+    uint32_t tot;
+    uint32_t at = block_scan_excl<NTH>(sum, tmp, &tot);
+    for (int i = 0; i < Q; ++i) {
+      uint32_t* pb = &bk[NB - 1 - (tid * Q + i)];
+      const uint32_t c = *pb;
+      *pb = at << 16 | c;
+      at += c;
+    }
+    return __syncthreads_or(big > kBucketMax) == 0;
+  };
+  if (!spread.template operator()<false>()) {
+    for (int b = tid; b < NB; b += NTH) bk[b] = 0u;
+    __syncthreads();
+    if (!spread.template operator()<true>()) {
+      // the pads (least of all keys) may lie over the buckets
+      const int P = next_pow2((int)n);
+      for (int i = (int)n + tid; i < P; i += NTH) e2[i] = make_int2(-1, 0x7FC00000);
+      __syncthreads();
+      // (keys in registers cost narrow blocks, several per CU, their occupancy)
+      if constexpr (NTH >= 1024) bitonic_sort_desc_fast<NTH>(reinterpret_cast<OrderedEntry*>(e2), P);
+      else bitonic_sort_desc<NTH>(reinterpret_cast<OrderedEntry*>(e2), P);
+      return;
     }
   }
-  __syncthreads();
-  // bk[b]: start of the bucket in descending order << 16 | its count
-  const int Q = NB / NTH;
-  uint32_t sum = 0, big = 0;
-  for (int i = 0; i < Q; ++i) {
-    const uint32_t c = bk[NB - 1 - (tid * Q + i)];
-    sum += c;
-    big = max(big, c);
-  }
-  uint32_t tot;
-  uint32_t at = block_scan_excl<NTH>(sum, tmp, &tot);
-  for (int i = 0; i < Q; ++i) {
-    uint32_t* pb = &bk[NB - 1 - (tid * Q + i)];
-    const uint32_t c = *pb;
-    *pb = at << 16 | c;
-    at += c;
-  }
-  if (__syncthreads_or(big > kBucketMax)) return false;
 #pragma unroll
   for (int j = 0; j < EPT; ++j)
     if ((uint32_t)(tid + j * NTH) < n) e2[(bk[bs[j] >> 16] >> 16) + (bs[j] & 0xFFFFu)] = e[j];
@@ -211,7 +239,6 @@ __device__ __forceinline__ bool order_entries(int2* e2, uint32_t n, float mn, fl
   for (int j = 0; j < EPT; ++j)
     if ((uint32_t)(tid + j * NTH) < n) e2[bs[j]] = e[j];
   __syncthreads();
-  return true;
 }
 
 // LDS layout of radix_select_row with nth threads: a 256-bin histogram per

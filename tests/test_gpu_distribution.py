@@ -29,6 +29,11 @@ def _rows(kind, nq, nk, seed):
         s[:, :nk] = np.exp(np.clip(20 * rng.standard_normal((nq, nk)), -87, 88)).astype(np.float32)
     elif kind == "infs":           # more infinities than k, both signs
         s[:, :nk] = rng.choice([np.inf, -np.inf, 0.0, -0.0, np.nan, 1.0], size=(nq, nk))
+    elif kind in ("sparse", "masked", "middle"):  # a few spread scores, the others 0 or -inf
+        s[:, :nk] = -np.inf if kind == "masked" else 0.0
+        hit = rng.random((nq, nk)) < 0.0002
+        v = rng.standard_normal(int(hit.sum()))
+        s[:, :nk][hit] = v if kind == "middle" else np.abs(v)
     return torch.from_numpy(s)
 
 
@@ -87,13 +92,49 @@ def test_scores_in_workspace_for_unsplit_rows(lib, nq, nk, k):
 # last with 4096 sort entries and the first with more
 @pytest.mark.parametrize("nq,nk,k", [(600, 3000, 100), (600, 16385, 2048), (40, 16384, 2049), (5, 70001, 8192),
                                      (3, 4097, 4096)])
-@pytest.mark.parametrize("kind", ["normal", "ties", "narrow", "heavy", "infs", "const"])
+@pytest.mark.parametrize("kind", ["normal", "ties", "narrow", "heavy", "infs", "const", "sparse", "masked", "middle"])
 def test_radix_rows(lib, nq, nk, k, kind):
     scores = _rows(kind, nq, nk, seed=nk + k)
     offs = workloads.causal_offsets(nq, nk)
     offs[0] = min(nk, k + 1)
     gi, gs = lt.topk_radix(scores.cuda(), k, nk, torch.from_numpy(offs).cuda(), sorted_output=True)
     _check(scores, nk, k, offs, None, gi.cpu().numpy(), gs.cpu().numpy(), True, sorted({0, 1, nq - 1}))
+
+
+# the k-th key shared by more keys than the sort slots hold: they are cut by
+# index, 64 keys at a time, n / 4096 from 2^18 keys on, and with parts past the
+# slots left (2^23) to the general selection
+@pytest.mark.parametrize("nq,nk,k", [(600, 16000, 33), (3, 5000, 2048), (2, 600001, 2048), (2, 600001, 5000),
+                                     (1, 9000001, 2048)])
+@pytest.mark.parametrize("kind", ["const", "sparse", "middle"])
+@pytest.mark.parametrize("sorted_out", [False, True])
+def test_radix_more_equal_keys_than_slots(lib, nq, nk, k, kind, sorted_out):
+    scores = _rows(kind, nq, nk, seed=nk)
+    s = scores[0, :nk].numpy()
+    assert np.sum(s == np.partition(s, nk - k)[nk - k]) > (12288 if k > 2048 else 3072)
+    if nq > 1:
+        scores[-1, :nk - 4000] = -5.0  # few of them, at the row's end
+    gi, gs = lt.topk_radix(scores.cuda(), k, nk, sorted_output=sorted_out)
+    _check(scores, nk, k, None, None, gi.cpu().numpy(), gs.cpu().numpy(), sorted_out, sorted({0, nq - 1}))
+
+
+# sorted rows whose kept keys no map spreads (more than 128 equal scores, of
+# several values): ordered by the sort in LDS. Scores in hand keep their bits
+# (both zeros), fused rows report canonical ones.
+@pytest.mark.parametrize("nq,nk,k", [(600, 9000, 700), (20, 9000, 700), (20, 40000, 3000), (600, 9000, 2048)])
+def test_sorted_rows_of_few_values(lib, nq, nk, k):
+    rng = np.random.default_rng(nk + k)
+    s = rng.choice([3.0, 2.0, 0.0, -0.0, -1.0], size=(nq, nk), p=[0.02, 0.02, 0.03, 0.03, 0.9]).astype(np.float32)
+    assert min(np.unique(np.sort(s[0])[-k:], return_counts=True)[1][1:]) > 128
+    scores = torch.from_numpy(s)
+    rows = [0, nq // 2, nq - 1]
+    for fn in (lambda: lt.topk_select(scores.cuda(), k, nk, options=lt.make_options(sorted_output=True)),
+               lambda: lt.topk_radix(scores.cuda(), k, nk, sorted_output=True)):
+        gi, gs = fn()
+        gi, gs = gi.cpu().numpy(), gs.cpu().numpy()
+        _check(scores, nk, k, None, None, gi, gs, True, rows)
+        for t in rows:
+            np.testing.assert_array_equal(gs[t].view(np.uint32), s[t][gi[t]].view(np.uint32))
 
 
 # candidate lists per row: one, fewer than a block's waves, more, and four
