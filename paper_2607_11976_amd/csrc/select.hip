@@ -1313,6 +1313,22 @@ __global__ __launch_bounds__(NTH, 4) void k_radix(const float* scores, int64_t s
                         flags & LT_SORTED_OUTPUT, lds);
 }
 
+// The same by radix_select_row alone, in narrow blocks (radix_digits). It sorts
+// no more than kRadixCollect keys of a digit's prefix: one pass more over such
+// rows costs less (3000 rows of 4096, k = 3000: 61 us, and 332 with up to 4096
+// keys sorted; 600 of 16384, k = 8192, scores around 10, 67 and 90).
+constexpr int kRadixCollect = 256;
+__global__ __launch_bounds__(kSelThreads) void k_radix_digits(const float* scores, int64_t stride, int nk,
+                                                              const int32_t* offs, int k, int32_t* out_i,
+                                                              float* out_s) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  const int row = blockIdx.x;
+  int e = offs ? offs[row] : nk;
+  e = e < 0 ? 0 : (e > nk ? nk : e);
+  radix_select_row<kSelThreads>(scores + (int64_t)row * stride, e, k, out_i + (int64_t)row * k,
+                                out_s + (int64_t)row * k, false, lds, 0, true, kRadixCollect);
+}
+
 // The fused path's dense fallback mode, second half: queued row t (flag 1)
 // was re-scored into scratch row t; one block selects it.
 __global__ __launch_bounds__(kSelThreads) void k_fallback_rows(const uint32_t* qctl, const int32_t* fbflag,
@@ -1453,9 +1469,30 @@ hipError_t launch_fallback_rows(const uint32_t* qctl, const int32_t* fbflag, con
   return hipGetLastError();
 }
 
+// Unsorted rows that radix_select_row takes from the start. Past k = 2048 the
+// buffer that orders them leaves room for one wide block per CU, and rows that
+// need no order are better off several to a CU, as long as they are short
+// against that ordering. us a call, k_radix and k_radix_digits, k = 4096, normal
+// scores (scores around 10): 3000 rows of 8192, 297 (298) and 78 (102); of
+// 16384, 319 (318) and 135 (142); of 32768, 366 (357) and 244 (264); of 65536,
+// 560 (547) and 502 (593); 512 rows of 16384, 57 (56) and 36 (40); of 32768, 65
+// (64) and 64 (79); 256 rows of 16384, 28 (28) and 33 (46).
+static bool radix_digits(int nq, int nk, int k) {
+  return k > 2048 &&
+         (nq > kSelFewRows ? nk <= 2 * kRadixShort : nq > 256 && nk <= kRadixShort);
+}
+
 hipError_t launch_radix(const float* scores, int64_t stride, int nq, int nk, const int32_t* offs,
                         int k, uint32_t flags, int32_t* out_i, float* out_s, hipStream_t st) {
   const int E = max(4096, 2 * next_pow2(k));
+  if (!(flags & LT_SORTED_OUTPUT) && radix_digits(nq, nk, k)) {
+    const size_t lds = radix_lds_bytes(kSelThreads, k);
+    if (lds > 65536)
+      (void)hipFuncSetAttribute((const void*)k_radix_digits, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k_radix_digits, dim3(nq), dim3(kSelThreads), lds, st, scores, stride, nk, offs, k, out_i,
+                       out_s);
+    return hipGetLastError();
+  }
   auto go = [&](auto kernel, int nth) {
     const size_t lds = radix_row_lds(nth, k, E);
     if (lds > 65536) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

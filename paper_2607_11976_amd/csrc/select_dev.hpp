@@ -300,16 +300,18 @@ __device__ __forceinline__ void sort_output_row(int32_t* oi, float* os, int n, u
 // the gathered digits in ascending key index, then the gathered ones in the
 // total order), or the total order when `sorted`.
 // pad = false: a row of n < k keys writes its n entries and nothing after.
+// collect: at most so many keys are gathered and sorted, where fewer than
+// radix_collect_cap(k).
 template <int NTH>
 __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k, int32_t* oi, float* os, bool sorted,
-                                                 uint8_t* lds, bool pad);
+                                                 uint8_t* lds, bool pad, int collect);
 
 // radix_select_row over keys [base, base + n) of a row whose key `base` is at
 // row[0]: the written indices are shifted by `base`.
 template <int NTH>
 __device__ __forceinline__ void radix_select_row(const float* row, int n, int k, int32_t* oi, float* os, bool sorted,
-                                 uint8_t* lds, int base = 0, bool pad = true) {
-  radix_select_row_at<NTH>(row, n, k, oi, os, sorted, lds, pad);
+                                 uint8_t* lds, int base = 0, bool pad = true, int collect = INT_MAX) {
+  radix_select_row_at<NTH>(row, n, k, oi, os, sorted, lds, pad, collect);
   if (base != 0) {
     __threadfence_block();
     __syncthreads();
@@ -345,7 +347,7 @@ __device__ __forceinline__ void split_fallback_select(const float* srow, int rs,
   __threadfence();
   int u = 0;
   for (int j = 0; j < chunks; ++j) u += min(k, clen(j));
-  radix_select_row_at<NTH>(cscore, u, k, oi, os, sorted, lds, true);
+  radix_select_row_at<NTH>(cscore, u, k, oi, os, sorted, lds, true, INT_MAX);
   __threadfence_block();
   __syncthreads();
   for (int i = threadIdx.x; i < k; i += NTH)
@@ -446,7 +448,7 @@ __device__ __noinline__ void radix_copy_short_row(const float* row, int n, int k
 // separate allocation keeps its unrolled loads from spilling the scan.
 template <int NTH>
 __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k, int32_t* oi, float* os, bool sorted,
-                                                 uint8_t* lds, bool pad) {
+                                                 uint8_t* lds, bool pad, int collect) {
   constexpr int NW = NTH / kWave, U = kRadixUnroll;
   static_assert(NW <= 16, "16 words of exchange per wave count");
   static_assert(NW >= 4, "segments of fewer than 2^30 keys");
@@ -478,7 +480,7 @@ __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k,
   uint32_t gbefore = 0;  // this wave's keys above the digits chosen so far (wave-uniform)
   uint32_t eqw = 0;      // this wave's keys == K* (after the last pass)
   uint32_t inbin = (uint32_t)n;  // keys with the digits chosen so far
-  const uint32_t cap = (uint32_t)radix_collect_cap(k);
+  const uint32_t cap = (uint32_t)min(radix_collect_cap(k), __builtin_amdgcn_readfirstlane(collect));
   bool collected = false;
   for (int pass = 0; pass < 4; ++pass) {
     if (inbin <= cap) {  // wave-uniform

@@ -101,6 +101,19 @@ def test_radix_rows(lib, nq, nk, k, kind):
     _check(scores, nk, k, offs, None, gi.cpu().numpy(), gs.cpu().numpy(), True, sorted({0, 1, nq - 1}))
 
 
+# unsorted rows of k > 2048: 8-bit digits alone for more than 256 rows of up to
+# 16384 keys and more than 512 of up to 32768
+@pytest.mark.parametrize("nq,nk,k", [(256, 5000, 2049), (257, 16384, 2049), (257, 16385, 4096), (513, 32768, 4097),
+                                     (513, 32769, 2100), (300, 2050, 2049), (300, 8193, 8192), (300, 16000, 2048)])
+@pytest.mark.parametrize("kind", ["normal", "ties", "infs", "middle"])
+def test_radix_unsorted_large_k(lib, nq, nk, k, kind):
+    scores = _rows(kind, nq, nk, seed=nk + k)
+    offs = workloads.causal_offsets(nq, nk)
+    offs[0] = k  # no more keys than k
+    gi, gs = lt.topk_radix(scores.cuda(), k, nk, torch.from_numpy(offs).cuda())
+    _check(scores, nk, k, offs, None, gi.cpu().numpy(), gs.cpu().numpy(), False, sorted({0, 1, nq - 1}))
+
+
 # the k-th key shared by more keys than the sort slots hold: they are cut by
 # index, 64 keys at a time, n / 4096 from 2^18 keys on, and with parts past the
 # slots left (2^23) to the general selection
