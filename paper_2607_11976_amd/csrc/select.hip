@@ -302,6 +302,7 @@ __global__ __launch_bounds__(NTH) void k_range(const float* src, int64_t stride,
 // row and one load in flight, 282 us so (3.8 TB/s).
 // ---------------------------------------------------------------------------
 constexpr int kRefreshShare = 4;
+constexpr int kFilterShort = 1024;  // splits of so many keys are one wave's
 constexpr int kFilterLong = 32768;  // splits of this many keys take 16 keys per thread and step, shorter ones 8
 
 template <int NTH, int U>
@@ -1390,9 +1391,17 @@ hipError_t launch_filter(const float* scores, int64_t stride, int nq, int nk, co
     hipLaunchKernelGGL(kernel, dim3(nq * S), dim3(nth), 0, st, scores, stride, nq, nk, offs, starts, params, S, L,
                        cap, m, k, cnt, hist, cand);
   };
-  // 16 waves per CU: one block of 1024 threads, two of 512 or four of 256
+  // 16 waves per CU: one block of 1024 threads, two of 512 or four of 256; a
+  // split of at most two steps of one wave is a wave's alone, for its block's
+  // barriers and empty waves cost more than its keys (unsorted: 100000 rows of
+  // 256 keys 1022 us a call in blocks of 256 threads, 855 in single waves; 300
+  // rows of 1024, 42 in blocks of 1024 and 36; 1200 rows of 2048, 29.7 and 32.8)
   const int units = nq * S;
   if (units == 0) return hipSuccess;
+  if (L <= kFilterShort) {
+    go(k_filter<kWave, 8>, kWave);
+    return hipGetLastError();
+  }
   auto by_len = [&](auto U) {
     constexpr int u = decltype(U)::value;
     if (units >= 1024) go(k_filter<256, u>, 256);

@@ -48,7 +48,7 @@ def _check(scores, nk, k, offs, starts, gi, gs, sorted_out, rows):
 
 
 # block widths follow the rows (1024, 512 and 256 threads from 1, 512 and 1024
-# units), steps the split's length (32768 keys); fewer than 256 rows split
+# units; one wave for up to 1024 keys), steps the split's length (32768 keys); fewer than 256 rows split
 @pytest.mark.parametrize("nq,nk,k,kind", [
     (1, 140001, 100, "normal"),
     (3, 70000, 2048, "ascending"),
@@ -58,6 +58,9 @@ def _check(scores, nk, k, offs, starts, gi, gs, sorted_out, rows):
     (1025, 4099, 100, "infs"),
     (1024, 40003, 16, "heavy"),
     (130, 257, 300, "normal"),
+    (300, 1024, 64, "ascending"),
+    (3, 1025, 20, "special"),
+    (2000, 255, 16, "infs"),
 ])
 @pytest.mark.parametrize("sorted_out", [False, True])
 def test_scores_in_filter_shapes(lib, nq, nk, k, kind, sorted_out):
