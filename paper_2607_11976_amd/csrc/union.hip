@@ -245,10 +245,14 @@ hipError_t launch_dsa_union(const int32_t* idx, int64_t ld, int nq, int k, int g
   };
   // small groups leave most of a wide block idle: 2048 lists of 256 keys alone
   // take 24 us in narrow blocks and 70 us in wide ones, 1024 pairs of lists of
-  // 1024 keys 20 us and 43 us
+  // 1024 keys 20 us and 43 us. Where few groups are that small, wide blocks
+  // with one entry per thread: 512 lists of 1024 keys 13.2 us (20.2 in the
+  // blocks of 16 entries), 16 of 64 13.2 (16.0)
   const int n = group * k;
   if (n <= kUnionSmall && groups > kUnionManyGroups)
     go(k_dsa_union<kUnionThreadsSmall, kUnionSmall / kUnionThreadsSmall>, kUnionThreadsSmall, kUnionLdsSmall);
+  else if (n <= kUnionThreads)
+    go(k_dsa_union<kUnionThreads, 1>, kUnionThreads, kUnionLds);
   else if (n <= LT_UNION_MAX / 2)
     go(k_dsa_union<kUnionThreads, LT_UNION_MAX / 2 / kUnionThreads>, kUnionThreads, kUnionLds);
   else

@@ -200,12 +200,15 @@ def test_fused_few_tiles(lib, nq, nk, h, d, dtype, mode, k, opt):
         check_row_exact(gi[t], gs[t], ri[j], rs[j], int(x["offsets"][t]), k, True)
 
 
-# spans around what the bitmap of a wide (2^20 keys and some) and of a narrow
+# one entry per thread up to 1024 entries a group (512 groups at most); spans
+# around what the bitmap of a wide (2^20 keys and some) and of a narrow
 # block holds, and keys up to the largest index
 @pytest.mark.parametrize("nq,k,group,span,top", [
     (16, 512, 8, 1 << 20, 1 << 20), (16, 512, 8, 1 << 21, 1 << 21), (16, 512, 8, 1000, 2 ** 31 - 1),
     (16, 512, 8, 2 ** 31 - 1, 2 ** 31 - 1), (1100, 64, 2, 200000, 300000), (1100, 64, 2, 400000, 400000),
-    (20, 2048, 16, 131072, 131072), (9, 3000, 3, 50000, 50000), (7, 1, 5, 3, 3)])
+    (20, 2048, 16, 131072, 131072), (9, 3000, 3, 50000, 50000), (7, 1, 5, 3, 3),
+    (18, 128, 8, 1 << 20, 1 << 20), (18, 128, 8, 1 << 21, 1 << 21), (18, 129, 8, 1 << 21, 1 << 21),
+    (512, 1023, 1, 131072, 131072), (513, 1023, 1, 131072, 131072)])
 def test_union_spans(lib, nq, k, group, span, top):
     rng = np.random.default_rng(k + group)
     idx = (top - span + rng.integers(0, span, size=(nq, k))).astype(np.int32)
