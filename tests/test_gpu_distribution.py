@@ -172,8 +172,8 @@ def test_fused_sorted_rows(lib, nq, splits, k):
 
 # launches of few query tiles: splits down to one key tile, rows whose lists
 # hold a whole split (no second pass), the fallback without its dense mode (up
-# to 128 rows; fewer keys than two chunks: whole rows), and a second pass over
-# splits that share thresholds
+# to 128 rows; fewer keys than two chunks: whole rows), and short lists of splits
+# that share thresholds
 @pytest.mark.parametrize("nq,nk,h,d,dtype,mode,k,opt", [
     (1, 64, 64, 128, "bf16", "dsa", 5, dict()),
     (3, 5000, 64, 128, "fp8", "dsa", 700, dict()),
@@ -196,6 +196,26 @@ def test_fused_few_tiles(lib, nq, nk, h, d, dtype, mode, k, opt):
     gi, gs = gi.cpu().numpy(), gs.cpu().numpy()
     rows = sorted({0, nq // 2, nq - 1})
     ri, rs, _ = oracle_topk(x, dtype, k, mode, rows=rows)
+    for j, t in enumerate(rows):
+        check_row_exact(gi[t], gs[t], ri[j], rs[j], int(x["offsets"][t]), k, True)
+
+
+# lists of 300 entries for k = 200: every row overflows one and is completed by
+# the second pass (row_stats reason 6), over splits that share thresholds
+@pytest.mark.parametrize("h,mode", [(1, "ip"), (4, "dsa")])
+def test_second_pass_over_shared_thresholds(lib, h, mode):
+    nq, nk, k = 40, 20000, 200
+    x = workloads.exact_inputs(nq, nk, h, 128, "bf16", seed=5)
+    if mode == "ip":
+        x["w"] = None
+    dev = to_dev(x)
+    stats = torch.full((nq, lt.LT_ROW_STATS), -7, dtype=torch.int32, device="cuda")
+    gi, gs = lt.indexer_topk(dev["q"], dev["w"], dev["keys"], k, dev["offsets"], mode=mode,
+                             options=lt.make_options(sorted_output=True, key_splits=4, capacity=300, row_stats=stats))
+    assert bool((stats[:, 2] == 6).all())
+    gi, gs = gi.cpu().numpy(), gs.cpu().numpy()
+    rows = [0, nq // 2, nq - 1]
+    ri, rs, _ = oracle_topk(x, "bf16", k, mode, rows=rows)
     for j, t in enumerate(rows):
         check_row_exact(gi[t], gs[t], ri[j], rs[j], int(x["offsets"][t]), k, True)
 
