@@ -108,9 +108,15 @@ typedef struct lt_options {
                               k + max(1024, k/2) for the 768-dimensional shapes,
                               whose splits share one threshold (for those shapes
                               rounded up to a multiple of 16: their lists are
-                              stored in chunks of 16 entries)                  */
+                              stored in chunks of 16 entries). Splits that the
+                              default key_splits adds to fill the GPU take
+                              shorter lists in the same memory: a slot for every
+                              key of the split, or with visible_start set no
+                              fewer than 6k. The scores-in entry takes at most a
+                              slot for every key of the split                   */
   int32_t key_splits;      /* key-range splits per row; 0 = auto (scores-in: 1 from 256
-                              rows on)                                           */
+                              rows on, and where the workspace has room for no
+                              more)                                             */
   uint32_t flags;          /* LT_SORTED_OUTPUT | LT_FORCE_FALLBACK               */
   uint64_t seed;           /* seed of the key sample                             */
   void** stage_events;     /* NULL, or LT_NUM_STAGE_EVENTS hipEvent_t handles     */

@@ -33,7 +33,7 @@ constexpr int kSampleBlockScores = 64;      // scores-in sample: runs of 64 cons
 constexpr int kMinScoresSplitKeys = 16384;  // shortest key split the scores-in entry makes by itself:
 constexpr int kMinScoresSplitK = 32;        // these keys, and this many times k
 constexpr int kFillKeys = 256;                // shortest key split made to fill the GPU (64 heads)
-constexpr int kPackedRounds = 4;              // blocks per CU aimed at for packed sequences
+constexpr int kPackedRounds = 4;              // blocks per CU that packed sequences take at most
 constexpr int kPackedCap = 6;                 // shortest candidate lists they get, in k
 constexpr int kMinSharedSplitKeys = 1024;   // shortest key split of the shared-row (wide) scan
 constexpr int kSharedSample = 65536;        // default sample of the shared-row scan (inner product)
@@ -214,10 +214,17 @@ Resolved resolve_fused(const lt_options* o, int nq, int nk, int k, int mode, con
     // workspace sized without visible_start serves with it, and no shape
     // outgrows the static one), their lists that much shorter:
     // * packed sequences: the tiles see ranges of different lengths, so blocks
-    //   of equal splits end at different times; kPackedRounds blocks per CU
-    //   even that out (1251 queries of four sequences of 3 to 41 K keys, bf16:
-    //   835, 786, 768, 736 us a call with 2, 3, 6, 8 splits). Lists of
-    //   kPackedCap * k entries at least, or the whole split.
+    //   of equal splits end at different times; more of them, up to
+    //   kPackedRounds blocks per CU, even that out (1251 queries of four
+    //   sequences of 3 to 41 K keys, bf16: 838, 779, 759, 750, 765, 714 us a
+    //   call with 2, 3, 4, 6, 7, 8 splits of full lists; the choice is 7 in the
+    //   memory of 3). Lists of kPackedCap * k entries at least, or the whole
+    //   split. Long key arrays that take one split above keep it: two lists of
+    //   6k and their histograms do not fit the memory of one list of 12k. Two
+    //   splits gain there where the sequences are ragged (2048 queries of
+    //   sequences of 100000, 31072 and 60000 keys: 2766 -> 2137 us) and lose
+    //   where they are equal (two of 131072 keys, 4096 queries: 6916 -> 7050;
+    //   four of 32768: 1976 -> 2062), and the lengths are on the GPU.
     // * launches that leave a third of the CUs idle or more: a block per CU, down
     //   to splits of kFillKeys keys (the grouped scans: one tile). Their lists
     //   hold the whole split. 64 queries of 4096 float32 keys: 117, 78, 70,

@@ -963,7 +963,7 @@ struct FusedSink {
 // alone, so no result depends on it.
 // Each 32-key sub-tile is gated on its own (margin, take), while the other
 // sub-tile's MFMAs run: gated together at the end of a tile, nothing of that
-// work was under a MFMA (10000 rows x 4M, k = 100: scan 11.4 -> 10.4 ms; a
+// work was under a MFMA (10000 rows x 4M, k = 100: scan 11.10 -> 10.17 ms; a
 // queue of 64 half-size records where 32 were: 1000 rows x 1M, k = 300, call
 // 2.47 -> 1.14 ms; 16 rows x 3M, k = 1000, 2.52 -> 1.31 ms).
 // Passing scores are not written out in the tile that finds them: every

@@ -1,7 +1,8 @@
 // LiteDSA's group union and per-query membership masks (sec. 3.3). One
 // block per group of consecutive queries, in one of two ways chosen by the
 // block from the span of its group's keys:
-//  * bitmap (the span fits the block's bitmap, up to 2^20 keys): every entry
+//  * bitmap (the span fits the block's bitmap, about 2^20 keys in wide blocks
+//    and 218000 in narrow ones): every entry
 //    sets its key's bit in LDS; a prefix sum of the population counts per 128
 //    keys gives each key its union slot, so the union comes out ascending and
 //    distinct, and each entry finds the bit of its query's mask with two LDS
@@ -247,7 +248,10 @@ hipError_t launch_dsa_union(const int32_t* idx, int64_t ld, int nq, int k, int g
   // take 24 us in narrow blocks and 70 us in wide ones, 1024 pairs of lists of
   // 1024 keys 20 us and 43 us. Where few groups are that small, wide blocks
   // with one entry per thread: 512 lists of 1024 keys 13.2 us (20.2 in the
-  // blocks of 16 entries), 16 of 64 13.2 (16.0)
+  // blocks of 16 entries), 16 of 64 13.2 (16.0). The host does not know the
+  // span: 1024 pairs of lists of 2048 keys take 23 us in narrow blocks within
+  // their bitmap and 122 to 125 past it, in the sort (164 to 172 in the wide
+  // blocks' sort alone)
   const int n = group * k;
   if (n <= kUnionSmall && groups > kUnionManyGroups)
     go(k_dsa_union<kUnionThreadsSmall, kUnionSmall / kUnionThreadsSmall>, kUnionThreadsSmall, kUnionLdsSmall);
