@@ -31,7 +31,6 @@ __global__ void k_init(uint32_t* qctl) {
 constexpr int kRangeThreads = 256;
 constexpr int kRangeThreadsLarge = 1024;  // samples of kRangeLargeSample keys or more, or few rows
 constexpr int kRangeLargeSample = 16384;
-constexpr int kFewRows = 512;  // launches of at most this many rows take wide blocks in the range stage and the radix select
 constexpr int kRangeUnroll = 8;
 constexpr int kRangeThreadsMid = 512;  // two blocks of them fit a CU with kRangeHold * 2 scores a thread
 constexpr int kRangeHold = 32, kRangeHoldFew = 8;  // sample scores a thread keeps in registers
@@ -440,7 +439,7 @@ constexpr int kSelThreads = 256;
 constexpr int kSelPer = 4;         // list entries per thread per step
 constexpr int kSelThreadsWide = 1024;  // keyed rows, and launches of few rows
 constexpr int kSelPerWide = 8;
-constexpr int kSelWideRows = 256;    // launches of at most this many rows use the wide blocks
+constexpr int kSelFewRows = 512;     // launches of at most this many rows use the wide blocks
 constexpr int kSecondSelectGrid = 512;  // blocks of the second select (persistent over its queue)
 
 // Threshold bins of at most this many keys are ranked by counting instead of
@@ -1368,15 +1367,15 @@ hipError_t launch_range(bool from_scores, const float* src, int64_t stride, int 
   // samples of 3000 rows: 40 us, 51 us read twice), but 64 of them in 1024
   // threads take a whole CU: many rows whose list is read too (40000 samples
   // of 1500 rows, causal: 106 us held, 88 us read twice) read them twice
-  const bool large = ns >= kRangeLargeSample || nq <= kFewRows;
+  const bool large = ns >= kRangeLargeSample || nq <= kSelFewRows;
   auto by_size = [&](auto FROM) {
     constexpr bool F = decltype(FROM)::value;
     if (!large && ns <= kRangeThreads * kRangeHold) go(k_range<kRangeThreads, F, kRangeHold>, kRangeThreads);
     else if (!large) go(k_range<kRangeThreads, F, 2 * kRangeHold>, kRangeThreads);
     else if (ns <= kRangeThreadsLarge * kRangeHoldFew) go(k_range<kRangeThreadsLarge, F, kRangeHoldFew>, kRangeThreadsLarge);
-    else if (nq > kFewRows && ns <= kRangeThreadsMid * 2 * kRangeHold) go(k_range<kRangeThreadsMid, F, 2 * kRangeHold>, kRangeThreadsMid);
+    else if (nq > kSelFewRows && ns <= kRangeThreadsMid * 2 * kRangeHold) go(k_range<kRangeThreadsMid, F, 2 * kRangeHold>, kRangeThreadsMid);
     else if (ns <= kRangeThreadsLarge * kRangeHold) go(k_range<kRangeThreadsLarge, F, kRangeHold>, kRangeThreadsLarge);
-    else if (ns <= kRangeThreadsLarge * 2 * kRangeHold && (F || !list || nq <= kFewRows))
+    else if (ns <= kRangeThreadsLarge * 2 * kRangeHold && (F || !list || nq <= kSelFewRows))
       go(k_range<kRangeThreadsLarge, F, 2 * kRangeHold>, kRangeThreadsLarge);
     else go(k_range<kRangeThreadsLarge, F, 0>, kRangeThreadsLarge);
   };
@@ -1426,14 +1425,13 @@ hipError_t launch_select(RowParam* params, const uint32_t* cnt, const uint32_t* 
     hipLaunchKernelGGL(kernel, dim3(nq), dim3(nth), lds, st, params, cnt, hist, cand, nq, S, HS, cap, m, k, E, flags,
                        out_i, out_s, qctl, queue, rqueue, rflag, pub, stats);
   };
-  // one block per row: up to a row per CU, wide blocks, whose more loads in
-  // flight shorten the walk over the lists; more rows share the CUs in narrow
-  // ones (a call, sorted, at 1024 and 256 threads: 256 rows of 65536 scores, k =
-  // 2048, 59.3 and 65.0 us, 257 rows 97.5 and 90.7; 512 rows of 16384, k = 100,
-  // 47.8 and 35.8, 4096 rows 240 and 117; 256 queries of 16384 bf16 keys, k =
-  // 1024, 112 and 116, 257 queries 138 and 131)
+  // one block per row: a launch of few rows (a short chunk) fills the GPU
+  // only with wide blocks, whose more loads in flight also shorten the walk
+  // over the lists; many rows fill it with narrow ones (measured on MI355X:
+  // 256 rows, 33 K candidates each, 1.57 -> 0.79 ms; 4096 rows with 8.7 K,
+  // 0.16 ms at 256 threads against 0.37 ms at 1024)
   // (and a sort buffer past 4096 entries leaves room for one block per CU)
-  if ((flags & kSelIlv) || nq <= kSelWideRows || E > 4096) go(k_select<kSelThreadsWide, kSelPerWide>, kSelThreadsWide);
+  if ((flags & kSelIlv) || nq <= kSelFewRows || E > 4096) go(k_select<kSelThreadsWide, kSelPerWide>, kSelThreadsWide);
   else go(k_select<kSelThreads, kSelPer>, kSelThreads);
   return hipGetLastError();
 }
@@ -1490,7 +1488,7 @@ hipError_t launch_fallback_rows(const uint32_t* qctl, const int32_t* fbflag, con
 // (64) and 64 (79); 256 rows of 16384, 28 (28) and 33 (46).
 static bool radix_digits(int nq, int nk, int k) {
   return k > 2048 &&
-         (nq > kFewRows ? nk <= 2 * kRadixShort : nq > 256 && nk <= kRadixShort);
+         (nq > kSelFewRows ? nk <= 2 * kRadixShort : nq > 256 && nk <= kRadixShort);
 }
 
 hipError_t launch_radix(const float* scores, int64_t stride, int nq, int nk, const int32_t* offs,
@@ -1511,7 +1509,7 @@ hipError_t launch_radix(const float* scores, int64_t stride, int nq, int nk, con
   };
   // many short rows: narrow blocks, several per CU; their 3072 sort slots
   // serve k <= 2048
-  if (nq > kFewRows && nk <= kRadixShort && E <= 4096)
+  if (nq > kSelFewRows && nk <= kRadixShort && E <= 4096)
     go(k_radix<kRadixThreadsSmall>, kRadixThreadsSmall);
   else
     go(k_radix<kRadixThreads>, kRadixThreads);

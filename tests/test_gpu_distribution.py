@@ -154,9 +154,9 @@ def test_sorted_rows_of_few_values(lib, nq, nk, k):
 
 
 # candidate lists per row: one, fewer than a block's waves, more, and four
-# times as many (16 waves up to 256 rows, 4 beyond); integer inputs give exact
+# times as many (16 waves up to 512 rows, 4 beyond); integer inputs give exact
 # scores with many ties
-@pytest.mark.parametrize("nq,splits", [(9, 1), (9, 3), (9, 17), (9, 64), (256, 17), (257, 17), (520, 2), (520, 5), (520, 16)])
+@pytest.mark.parametrize("nq,splits", [(9, 1), (9, 3), (9, 17), (9, 64), (520, 2), (520, 5), (520, 16)])
 @pytest.mark.parametrize("k", [50, 2100])
 def test_fused_sorted_rows(lib, nq, splits, k):
     x = workloads.exact_inputs(nq, 5000, 64, 128, "bf16", seed=nq + splits)
