@@ -1326,8 +1326,8 @@ __global__ __launch_bounds__(kSelThreads) void k_radix_digits(const float* score
   const int row = blockIdx.x;
   int e = offs ? offs[row] : nk;
   e = e < 0 ? 0 : (e > nk ? nk : e);
-  radix_select_row<kSelThreads>(scores + (int64_t)row * stride, e, k, out_i + (int64_t)row * k,
-                                out_s + (int64_t)row * k, false, lds, 0, true, kRadixCollect);
+  radix_select_row<kSelThreads, kRadixCollect>(scores + (int64_t)row * stride, e, k, out_i + (int64_t)row * k,
+                                               out_s + (int64_t)row * k, false, lds);
 }
 
 // The fused path's dense fallback mode, second half: queued row t (flag 1)
@@ -1427,9 +1427,12 @@ hipError_t launch_select(RowParam* params, const uint32_t* cnt, const uint32_t* 
   };
   // one block per row: a launch of few rows (a short chunk) fills the GPU
   // only with wide blocks, whose more loads in flight also shorten the walk
-  // over the lists; many rows fill it with narrow ones (measured on MI355X:
-  // 256 rows, 33 K candidates each, 1.57 -> 0.79 ms; 4096 rows with 8.7 K,
-  // 0.16 ms at 256 threads against 0.37 ms at 1024)
+  // over the lists; many rows fill it with narrow ones. A call at 1024 and 256
+  // threads: 256 rows of 65536 scores, k = 2048, sorted, 59 and 65 us; 4096 of
+  // 16384, k = 100, 240 and 117. From 257 to 512 rows either may win: 512 rows
+  // of 16384, k = 100, 47 and 36; but 300 queries of 65536 keys, k = 2048, no
+  // sample, 892 and 1018, 300 of 100000 (inner product), k = 1000, 316 and 335,
+  // and 512 rows of 131072 multiples of 1/8, k = 2048, 211 and 231
   // (and a sort buffer past 4096 entries leaves room for one block per CU)
   if ((flags & kSelIlv) || nq <= kSelFewRows || E > 4096) go(k_select<kSelThreadsWide, kSelPerWide>, kSelThreadsWide);
   else go(k_select<kSelThreads, kSelPer>, kSelThreads);

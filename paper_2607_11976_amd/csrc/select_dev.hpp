@@ -300,18 +300,18 @@ __device__ __forceinline__ void sort_output_row(int32_t* oi, float* os, int n, u
 // the gathered digits in ascending key index, then the gathered ones in the
 // total order), or the total order when `sorted`.
 // pad = false: a row of n < k keys writes its n entries and nothing after.
-// collect: at most so many keys are gathered and sorted, where fewer than
+// COLLECT: at most so many keys are gathered and sorted, where fewer than
 // radix_collect_cap(k).
-template <int NTH>
+template <int NTH, int COLLECT = INT_MAX>
 __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k, int32_t* oi, float* os, bool sorted,
-                                                 uint8_t* lds, bool pad, int collect);
+                                                 uint8_t* lds, bool pad);
 
 // radix_select_row over keys [base, base + n) of a row whose key `base` is at
 // row[0]: the written indices are shifted by `base`.
-template <int NTH>
+template <int NTH, int COLLECT = INT_MAX>
 __device__ __forceinline__ void radix_select_row(const float* row, int n, int k, int32_t* oi, float* os, bool sorted,
-                                 uint8_t* lds, int base = 0, bool pad = true, int collect = INT_MAX) {
-  radix_select_row_at<NTH>(row, n, k, oi, os, sorted, lds, pad, collect);
+                                 uint8_t* lds, int base = 0, bool pad = true) {
+  radix_select_row_at<NTH, COLLECT>(row, n, k, oi, os, sorted, lds, pad);
   if (base != 0) {
     __threadfence_block();
     __syncthreads();
@@ -347,7 +347,7 @@ __device__ __forceinline__ void split_fallback_select(const float* srow, int rs,
   __threadfence();
   int u = 0;
   for (int j = 0; j < chunks; ++j) u += min(k, clen(j));
-  radix_select_row_at<NTH>(cscore, u, k, oi, os, sorted, lds, true, INT_MAX);
+  radix_select_row_at<NTH>(cscore, u, k, oi, os, sorted, lds, true);
   __threadfence_block();
   __syncthreads();
   for (int i = threadIdx.x; i < k; i += NTH)
@@ -446,9 +446,9 @@ __device__ __noinline__ void radix_copy_short_row(const float* row, int n, int k
 
 // Not inlined: the callers inline it after a register-heavy scan, and a
 // separate allocation keeps its unrolled loads from spilling the scan.
-template <int NTH>
+template <int NTH, int COLLECT>
 __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k, int32_t* oi, float* os, bool sorted,
-                                                 uint8_t* lds, bool pad, int collect) {
+                                                 uint8_t* lds, bool pad) {
   constexpr int NW = NTH / kWave, U = kRadixUnroll;
   static_assert(NW <= 16, "16 words of exchange per wave count");
   static_assert(NW >= 4, "segments of fewer than 2^30 keys");
@@ -480,7 +480,7 @@ __device__ __noinline__ void radix_select_row_at(const float* row, int n, int k,
   uint32_t gbefore = 0;  // this wave's keys above the digits chosen so far (wave-uniform)
   uint32_t eqw = 0;      // this wave's keys == K* (after the last pass)
   uint32_t inbin = (uint32_t)n;  // keys with the digits chosen so far
-  const uint32_t cap = (uint32_t)min(radix_collect_cap(k), __builtin_amdgcn_readfirstlane(collect));
+  const uint32_t cap = (uint32_t)min(radix_collect_cap(k), COLLECT);
   bool collected = false;
   for (int pass = 0; pass < 4; ++pass) {
     if (inbin <= cap) {  // wave-uniform
